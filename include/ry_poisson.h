@@ -12,7 +12,11 @@
  * neighbour), boundary periodic or zero Dirichlet.  The preconditioner is
  * applied as the matrix M^-1 with the same boundary rule; RY_PC_NONE gives
  * the pipelined form of plain CG (M^-1 = I).  A periodic problem is
- * singular: b must have zero sum for the iteration to converge.
+ * singular: b must have zero sum for the iteration to converge.  The
+ * iterates, scalars and vectors below are the method's for every size;
+ * problems of at least 5 * 2^18 cells are iterated in a form that keeps x, r
+ * and p only and applies M^-1 and A where the recurrences would carry u, w,
+ * s, q and z (equal in exact arithmetic, half the memory traffic).
  *
  * Conventions: every function returns a ry_status (include/ry.h); host
  * pointers are borrowed for the duration of the call; device memory belongs
@@ -48,8 +52,8 @@ typedef struct {
 
 typedef struct ry_poisson ry_poisson;
 
-/* Allocates nine FP64 grid vectors (x, r, u, w twice, z, q, s, p) plus
- * reduction scratch and an eps history of RY_POISSON_HIST entries.
+/* Allocates nine FP64 grid vectors (x, r, u, w twice, z, q, s, p; from
+ * 5 * 2^18 cells on five: x, r twice, p twice) plus reduction scratch and an eps history of RY_POISSON_HIST entries.
  * RY_EINVAL: bad sizes or enums; RY_ENOMEM: allocation failed (nothing
  * leaks); RY_EHIP: no device. */
 #define RY_POISSON_HIST 65536
@@ -78,16 +82,17 @@ ry_status ry_poisson_iterate(ry_poisson* p, int32_t n);
 ry_status ry_poisson_eps_history(ry_poisson* p, double* eps, int32_t cap, int32_t* n);
 
 /* Copy one recurrence vector (RY_PV_*) to the host (n0*n1*n2 doubles, x
- * fastest).  RY_PV_X is the current iterate.  Syncs. */
+ * fastest), formed on the device first where it is not kept.  RY_PV_X is the
+ * current iterate.  Syncs. */
 ry_status ry_poisson_download(ry_poisson* p, int32_t which, double* host);
 
 /* Scalars carried between iterations: alpha_{i-1}, gamma_{i-1} and i.  Syncs. */
 ry_status ry_poisson_scalars(ry_poisson* p, double* alpha_prev, double* gamma_prev, int32_t* iter);
 
-/* Kernel timing: when on, every iteration kernel is bracketed by HIP events
- * on the solver's stream; ry_poisson_kernel_time returns the number of
- * timed launches and their summed duration (ms) since timing was switched
- * on.  Syncs. */
+/* Kernel timing: when on, every iteration (one kernel, or the two sweeps of
+ * the large problems) is bracketed by HIP events on the solver's stream;
+ * ry_poisson_kernel_time returns the number of timed iterations and their
+ * summed duration (ms) since timing was switched on.  Syncs. */
 ry_status ry_poisson_set_timing(ry_poisson* p, int32_t on);
 ry_status ry_poisson_kernel_time(ry_poisson* p, int32_t* launches, double* total_ms);
 

@@ -1,24 +1,38 @@
-// Uniform-level Poisson solver on gfx950: the preconditioned pipelined
-// conjugate-gradient method (PPCG; Ghysels & Vanroose 2014, Algorithm 4)
-// with the seven-point preconditioner 13/12 (centre), 1/6 (face neighbours).
+// Uniform-level Poisson solver on gfx950: the preconditioned conjugate-
+// gradient iterates of PPCG (Ghysels & Vanroose 2014, Algorithm 4) with the
+// seven-point preconditioner 13/12 (centre), 1/6 (face neighbours), in one of
+// two forms chosen by the problem's size (kTwoSweepCells):
 //
-// One iteration i is two launches on the solver's stream:
-//   finalize  sums the per-workgroup partials of gamma_i = r_i.u_i and
-//             delta_i = w_i.u_i in a fixed order, records eps_i, tests
-//             convergence and forms alpha_i, beta_i on the device;
-//   iterate   a z-marching stencil sweep that, per cell, forms
-//             m_i = M^-1 w_i and n_i = A m_i from w_i staged in LDS, updates
-//             the eight recurrence vectors (z, q, s, p, then x, r, u, w) and
-//             accumulates the partials of gamma_{i+1}, delta_{i+1}.
-// So each iteration reads and writes every recurrence vector once (8 + 8
-// FP64 values per cell), with one device-wide reduction, which is the
-// single synchronisation per iteration the pipelined method is built for.
-// w is double-buffered (neighbouring workgroups read w_i while w_{i+1} is
-// written); every other vector is updated in place.
+// Pipelined form (small problems: each launch counts, the vectors sit in the
+// caches).  One launch per iteration i: every workgroup sums the partials of
+// gamma_i = r_i.u_i and delta_i = w_i.u_i that the launch before left, in
+// one fixed order, and forms alpha_i and beta_i itself; then a z-marching
+// stencil sweep forms m_i = M^-1 w_i and n_i = A m_i from w_i staged in LDS,
+// updates the eight recurrence vectors (z, q, s, p, then x, r, u, w) and
+// leaves the partials of gamma_{i+1}, delta_{i+1}.  128 bytes per cell.
 //
-// Iteration kernel geometry: a workgroup owns a TX x TY column of cells and
-// a chunk of z planes; it keeps five w planes (2-cell halo in x, y) and
-// three m planes (1-cell halo) in LDS as a rolling window.
+// Two-sweep form (large problems: HBM bandwidth counts).  The same iterates
+// with the fewest vectors streamed: u = M^-1 r, s = A p, q = M^-1 s, z = A q
+// and w = A u hold by definition, so only x, r and p are kept and the others
+// are applied on the fly, or formed when asked for:
+//   direction  p_i = M^-1 r_i + beta_i p_{i-1} on the tile and its one-cell
+//              halo, partials of p_i.(A p_i);
+//   update     r_{i+1} = r_i - alpha_i A p_i on the tile and its one-cell
+//              halo, x_{i+1}, partials of gamma_{i+1} = r_{i+1}.(M^-1 r_{i+1}).
+// 64 bytes per cell (r, p read and p written; p, r, x read and r, x written).
+// r and p are double-buffered: neighbouring workgroups read the old one.
+// Measured per iteration: 256^3 238 us (pipelined, with its scalar step in a
+// launch of its own: 420; a 1 GiB device copy runs at 5.07 TB/s, at which 64
+// bytes per cell take 212 us), 160^3 60 us (117), 128^3 40 us (60).
+//
+// Kernel geometry of all sweeps: a workgroup owns a TX x TY column of cells
+// and a chunk of z planes.  Every point of the plane with its two-cell halo
+// has a thread of its own, so the neighbours along z are the thread's own
+// registers, those in the plane are four LDS reads per stencil, and no lane
+// branches: a lane outside the grid loads a clamped address and selects 0.
+// The second stencil of a sweep runs one plane behind the first; with both
+// planes double-buffered in LDS one barrier per plane orders everything.
+// Loads run two planes ahead of their use.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -34,23 +48,55 @@
 namespace ryp {
 
 
-constexpr int TX = 32, TY = 8, NTH = TX * TY;
-constexpr int WX = TX + 4, WY = TY + 4, WPL = WX * WY;   // w plane, 2-cell halo
-constexpr int MX = TX + 2, MY = TY + 2, MPL = MX * MY;   // m plane, 1-cell halo
-constexpr int BATCH = 16;                                // iterations per captured graph
-constexpr int NVEC = 9;                                  // x r u w0 w1 z q s p
+// A TX x TY tile: the plane with its halo and its threads (two-sweep form).
+// 32 x 16: of 32 x 10, 32 x 16, 32 x 24 and 60 x 12 the fastest (256^3: 301,
+// 238, 279, 301 us per iteration): two 768-thread workgroups per CU, whole
+// tiles on the usual sides.
+template <int TX_, int TY_>
+struct Tile {
+  static constexpr int TX = TX_, TY = TY_, EX = TX + 4, EY = TY + 4;
+  static constexpr int NT = (EX * EY + 63) / 64 * 64, NWV = NT / 64;
+  static constexpr int PL = NT + 2 * EX;   // an LDS plane: every thread's four neighbours exist
+};
+using SmallTile = Tile<32, 8>;             // pipelined form
+using LargeTile = Tile<32, 16>;            // two-sweep form
+constexpr int NTH = 256;                   // threads of the whole-vector kernels
+constexpr int BATCH = 16;                                // iterations per captured graph (even: see step[])
+constexpr int NVEC = 9;                                  // pipelined: x r u w0 w1 z q s p; two-sweep: x r0 r1 p0 p1
+// Cells from which the two-sweep form is the faster one: its second launch
+// and reduction cost about 8 us an iteration more, its halved traffic gains
+// more than that from here on (both forms, us per iteration: 96^3 22.3
+// pipelined / 28.2 two-sweep, 101 x 99 x 103 29.0 / 32.7, 128^3 44.4 / 39.6,
+// 160^3 105 / 60).
+constexpr int64_t kTwoSweepCells = int64_t(5) << 18;
+// Workgroups per sweep at most (z chunks are added up to it).  Large: two per
+// CU, all resident, no second round.  Small: each workgroup pays the scalar
+// step and four halo planes, so few, thicker chunks (64^3: 11.3 us per
+// iteration with 512, 15.5 with 1024, 11.8 with 256).
+constexpr int kTargetSmall = 512, kTargetLarge = 512;
 
 struct Grid {
   int32_t n0, n1, n2, bc;
 };
 
-// Scalars carried between launches, device-resident.
+// Scalars carried between launches, device-resident.  A kernel's workgroups
+// all read what one of them writes for the next launch, so nothing is read
+// and written by the same kernel: the pipelined iteration i reads
+// step[i & 1] and writes step[1 - (i & 1)] (the host knows i, so the slot is
+// a launch argument); of the two-sweep form the direction kernel reads
+// step[0] and writes dir, the update kernel the other way round.  Once the
+// solve has stopped, the launches left in a graph only pass `done` on.
 struct Scalars {
-  double gamma0, alpha, beta, alpha_prev, gamma_prev, eps_target;
-  int32_t iter;      // index i of the next finalize
-  int32_t max_iter;  // stop when i reaches it
-  int32_t done;
-  int32_t src;       // buffer holding w_i for the iteration kernel
+  double gamma0, eps_target;
+  struct Step {
+    double alpha_prev, gamma_prev;
+    int32_t iter, done;   // index of the next iterate to test
+  } step[2];
+  struct Dir {
+    double gamma;
+    int32_t iter, done;
+  } dir;
+  int32_t max_iter;       // stop when the iterate's index reaches it
 };
 
 struct IterArgs {
@@ -58,8 +104,19 @@ struct IterArgs {
   double* w[2];
   double *x, *r, *u, *z, *q, *s, *p;
   Scalars* sc;
-  double* part;   // [2][gridDim.x]
+  double* hist;
+  double* part;   // two sets (by parity) of [2][gridDim.x]
   int32_t cz;     // z planes per workgroup
+  int32_t par;    // parity of the iteration index
+};
+
+struct CgArgs {
+  Grid g;
+  double *x, *r[2], *p[2];
+  Scalars* sc;
+  double* hist;
+  double *part_g, *part_d;   // [gridDim.x] each
+  int32_t cz;
 };
 
 __device__ __forceinline__ int wrap(int i, int n) {
@@ -93,234 +150,493 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblocks) {
   return x * q + (x < r ? x : r) + j;
 }
 
-// Block-wide sums of (a, b) -> part[blockIdx.x], part[gridDim.x + blockIdx.x],
-// in a fixed order.
-__device__ __forceinline__ void block_partials(double a, double b, double* part) {
-  __shared__ double red[2][NTH / 64];
-  a = wave_sum(a);
-  b = wave_sum(b);
+// Block-wide sum of NQ values per thread over the NWV wavefronts, to every
+// thread, in a fixed order.
+template <int NQ, int NWV>
+__device__ __forceinline__ void block_sum(double (&v)[NQ], double (*red)[NWV]) {
   const int wv = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
-    red[0][wv] = a;
-    red[1][wv] = b;
+#pragma unroll
+  for (int k = 0; k < NQ; ++k) {
+    v[k] = wave_sum(v[k]);
+    if ((threadIdx.x & 63) == 0) red[k][wv] = v[k];
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double sa = 0.0, sb = 0.0;
-    for (int k = 0; k < NTH / 64; ++k) {
-      sa += red[0][k];
-      sb += red[1][k];
-    }
-    part[blockIdx.x] = sa;
-    part[gridDim.x + blockIdx.x] = sb;
+#pragma unroll
+  for (int k = 0; k < NQ; ++k) {
+    v[k] = 0.0;
+#pragma unroll
+    for (int j = 0; j < NWV; ++j) v[k] += red[k][j];
   }
 }
 
+// A thread's share of the sum of n partials over NTH threads: fixed order,
+// loads in flight together.
+__device__ __forceinline__ double strided_sum(const double* __restrict__ part, int n) {
+  double a[4] = {};
+  for (int k = threadIdx.x; k - int(threadIdx.x) < n; k += 4 * NTH) {
+    double v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = part[min(k + j * NTH, n - 1)];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) a[j] += k + j * NTH < n ? v[j] : 0.0;
+  }
+  return (a[0] + a[1]) + (a[2] + a[3]);
+}
+
+// Sum of n partials by one wavefront, to each of its lanes: fixed order,
+// loads in flight together.
+__device__ __forceinline__ double wave_total(const double* __restrict__ part, int n) {
+  const int lane = threadIdx.x & 63;
+  double a[8] = {};
+  for (int k = lane; k - lane < n; k += 8 * 64) {
+    double v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = part[min(k + j * 64, n - 1)];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) a[j] += k + j * 64 < n ? v[j] : 0.0;
+  }
+  return wave_sum(((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7])));
+}
+
+// eps_i = sqrt(gamma_i / gamma_0) and whether the solve stops at iterate i.
+__device__ __forceinline__ bool stop_at(const Scalars* sc, int i, double gamma, double& eps) {
+  const double g0 = (i == 0) ? gamma : sc->gamma0;
+  eps = (g0 > 0.0 && gamma > 0.0) ? sqrt(gamma / g0) : 0.0;
+  return eps <= sc->eps_target || i >= sc->max_iter || i >= RY_POISSON_HIST - 1;
+}
+
+// The column of a workgroup: its first cell, its z planes, and the boundary
+// rule.  DOWN: the chunk's planes are marched from the last to the first (the
+// stencils are symmetric, so a sweep only sees other planes).
+template <typename T, bool DOWN = false>
+struct Chunk {
+  int x0, y0, z0, z1, n2;
+  bool periodic;
+  int64_t plane;
+  __device__ __forceinline__ Chunk(const Grid& g, int cz) {
+    const int gx = (g.n0 + T::TX - 1) / T::TX, gy = (g.n1 + T::TY - 1) / T::TY;
+    const int b = xcd_remap(blockIdx.x, gridDim.x);
+    x0 = (b % gx) * T::TX;
+    y0 = ((b / gx) % gy) * T::TY;
+    z0 = (b / (gx * gy)) * cz;
+    z1 = min(z0 + cz, g.n2);
+    n2 = g.n2;
+    plane = int64_t(g.n0) * g.n1;
+    periodic = g.bc == RY_PBC_PERIODIC;
+  }
+  __device__ __forceinline__ bool inside(const Grid& g, int X, int Y) const {
+    return periodic || (X >= 0 && X < g.n0 && Y >= 0 && Y < g.n1);
+  }
+  // index in a grid plane of the point (X, Y) of the tile with its halo, or
+  // of its periodic image; off a Dirichlet grid the nearest cell's
+  __device__ __forceinline__ int index(const Grid& g, int X, int Y) const {
+    if (periodic) {
+      // past the halo of the last cell nothing is read: one period at most
+      X = min(X, g.n0 + 1);
+      Y = min(Y, g.n1 + 1);
+      X = g.n0 == 1 ? 0 : (X < 0 ? X + g.n0 : (X >= g.n0 ? X - g.n0 : X));
+      Y = g.n1 == 1 ? 0 : (Y < 0 ? Y + g.n1 : (Y >= g.n1 ? Y - g.n1 : Y));
+    } else {
+      X = min(max(X, 0), g.n0 - 1);
+      Y = min(max(Y, 0), g.n1 - 1);
+    }
+    return X + g.n0 * Y;
+  }
+  // the grid's plane number of the march's plane z
+  __device__ __forceinline__ int number(int z) const { return DOWN ? z0 + z1 - 1 - z : z; }
+  // whether plane z is in the grid (or its continuation)
+  __device__ __forceinline__ bool inz(int z) const { return periodic || unsigned(number(z)) < unsigned(n2); }
+  // offset of the grid plane that plane z is (a neighbour of the grid: clamped)
+  __device__ __forceinline__ int64_t at(int z) const {
+    z = number(z);
+    if (unsigned(z) >= unsigned(n2)) z = periodic ? wrap(z, n2) : (z < 0 ? 0 : n2 - 1);
+    return plane * z;
+  }
+};
+
+// A thread's point of its workgroup's column.  ix2: its index in a grid
+// plane (any point with the two-cell halo); ix1, ix0: the index of the
+// nearest point of the one-cell halo and of the tile's own cells, which a
+// lane further out loads instead (no lines of its own).  in: inside the grid
+// (or its periodic continuation); own: one of the tile's cells.
+template <typename T, bool DOWN = false>
+struct Point : Chunk<T, DOWN> {
+  using C = Chunk<T, DOWN>;
+  using C::z0, C::z1, C::plane, C::at, C::inz, C::number;
+  int c, ix2, ix1, ix0;
+  bool in, own;
+  __device__ __forceinline__ Point(const Grid& g, int cz) : C(g, cz) {
+    const int t = threadIdx.x, lx = t % T::EX - 2, ly = t / T::EX - 2;   // ly past the tile's halo: spare lanes
+    c = t + T::EX;
+    const int X = C::x0 + lx, Y = C::y0 + ly;
+    own = lx >= 0 && lx < T::TX && ly >= 0 && ly < T::TY && X < g.n0 && Y < g.n1;
+    in = C::inside(g, X, Y);
+    auto into = [&](int h) {
+      return C::index(g, C::x0 + min(max(lx, -h), T::TX - 1 + h), C::y0 + min(max(ly, -h), T::TY - 1 + h));
+    };
+    ix2 = into(2);
+    ix1 = into(1);
+    ix0 = min(C::x0 + min(max(lx, 0), T::TX - 1), g.n0 - 1) +
+          g.n0 * min(C::y0 + min(max(ly, 0), T::TY - 1), g.n1 - 1);
+  }
+  // v at plane z (0 off the grid), loaded for every lane; planes past the
+  // last one the chunk reads are that one again
+  __device__ __forceinline__ double load2(const double* __restrict__ v, int z) const {
+    z = min(z, z1 + 1);
+    const double a = v[at(z) + ix2];
+    return (in && inz(z)) ? a : 0.0;
+  }
+  // the chunk's planes and one either side, one-cell halo
+  __device__ __forceinline__ double load1(const double* __restrict__ v, int z) const { return v[at(min(z, z1)) + ix1]; }
+  // the chunk's own cells
+  __device__ __forceinline__ int64_t cell(int z) const { return plane * number(max(z0, min(z, z1 - 1))) + ix0; }
+};
+
+// The four in-plane neighbours of point c in an LDS plane, then the ones
+// below and above.
+template <typename T>
+__device__ __forceinline__ double six(const double* pl, int c, double below, double above) {
+  double s = pl[c - 1];
+  s += pl[c + 1];
+  s += pl[c - T::EX];
+  s += pl[c + T::EX];
+  s += below;
+  s += above;
+  return s;
+}
+
 // ---------------------------------------------------------------------------
-// The iteration kernel.
+// The pipelined iteration.  Bound: at the sizes it serves, the chain of one
+// launch; everything the first plane needs is requested together, before
+// the partials' reduction, and the scalar step costs no launch of its own
+// (48 x 40 x 36: 8.2 us per iteration, 12.7 with a one-workgroup launch for
+// the scalars and loads issued plane by plane; 64^3 11.3, was 15.4; 96^3
+// 22.3, was 34.7).  One thread per cell and two rounds over the halo points:
+// a thread per halo point costs more wavefronts, whose prologue is what
+// counts here (48 x 40 x 36 9.9 us).
 // ---------------------------------------------------------------------------
 template <int PC>
 __global__ __launch_bounds__(NTH) void ppcg_iterate_kernel(IterArgs A) {
-  const Scalars* sc = A.sc;
-  if (sc->done) return;
-  __shared__ double Wp[5][WPL];
-  __shared__ double Mp[3][MPL];
+  constexpr int TX = SmallTile::TX, TY = SmallTile::TY;
+  constexpr int WX = TX + 4, WPL = WX * (TY + 4), NW = (WPL + NTH - 1) / NTH;   // planes with a 2-cell halo
+  constexpr int MX = TX + 2, MPL = MX * (TY + 2), NM = (MPL + NTH - 1) / NTH;   // and a 1-cell halo
+  static_assert(TX * TY == NTH, "one thread per cell");
+  __shared__ double Wp[5][WPL], Mp[3][MPL];
+  __shared__ double red[2][NTH / 64];
+  Scalars* sc = A.sc;
   const Grid g = A.g;
-  const bool periodic = g.bc == RY_PBC_PERIODIC;
-  const int gx = (g.n0 + TX - 1) / TX, gy = (g.n1 + TY - 1) / TY;
-  const int b = xcd_remap(blockIdx.x, gridDim.x);
-  const int bx = b % gx, by = (b / gx) % gy, bz = b / (gx * gy);
-  const int x0 = bx * TX, y0 = by * TY, z0 = bz * A.cz;
-  const int z1 = min(z0 + A.cz, g.n2);
+  const Chunk<SmallTile> C(g, A.cz);
   const int tid = threadIdx.x, tx = tid % TX, ty = tid / TX;
-  const double alpha = sc->alpha, beta = sc->beta;
-  const int src = sc->src;
-  const double* __restrict__ win = A.w[src];
-  double* __restrict__ wout = A.w[src ^ 1];
-
+  const int nb = gridDim.x;
+  const double* part_in = A.part + int64_t(A.par) * 2 * nb;
+  double* part_out = A.part + int64_t(A.par ^ 1) * 2 * nb;
+  const double* __restrict__ win = A.w[A.par];
+  double* __restrict__ wout = A.w[A.par ^ 1];
+  const bool own = C.x0 + tx < g.n0 && C.y0 + ty < g.n1;
+  const int64_t col = min(C.x0 + tx, g.n0 - 1) + int64_t(g.n0) * min(C.y0 + ty, g.n1 - 1);
+  // the thread's points of a plane with the 2-cell halo: a grid index each
+  // (off a Dirichlet grid: some index, and 0 selected)
+  int ixw[NW];
+  bool inw[NW], inm[NM];
+#pragma unroll
+  for (int j = 0; j < NW; ++j) {
+    const int k = min(tid + j * NTH, WPL - 1), X = C.x0 - 2 + k % WX, Y = C.y0 - 2 + k / WX;
+    ixw[j] = C.index(g, X, Y);
+    inw[j] = C.inside(g, X, Y);
+  }
+#pragma unroll
+  for (int j = 0; j < NM; ++j) {
+    const int k = tid + j * NTH;
+    inm[j] = C.inside(g, C.x0 - 1 + k % MX, C.y0 - 1 + k / MX);
+  }
+  auto load_w = [&](int z, double (&v)[NW]) {
+    const double* pl = win + C.at(z);
+    const bool ok = C.inz(z);
+#pragma unroll
+    for (int j = 0; j < NW; ++j) v[j] = pl[ixw[j]];
+#pragma unroll
+    for (int j = 0; j < NW; ++j) v[j] = ok && inw[j] ? v[j] : 0.0;
+  };
+  struct Rec {
+    double z, q, s, p, u, x, r;
+  };
+  auto load_rec = [&](int z) {
+    const int64_t i = col + C.plane * z;
+    return Rec{A.z[i], A.q[i], A.s[i], A.p[i], A.u[i], A.x[i], A.r[i]};
+  };
+  // the first plane's five w planes and recurrences, and the partials
+  double wr[5][NW];
+#pragma unroll
+  for (int k = 0; k < 5; ++k) load_w(C.z0 - 2 + k, wr[k]);
+  Rec rec = load_rec(C.z0), nxt{};
+  double gd[2] = {strided_sum(part_in, nb), strided_sum(part_in + nb, nb)};
+  // looked at with the loads under way
+  const Scalars::Step st = sc->step[A.par];
+  if (st.done) {
+    if (blockIdx.x == 0 && tid == 0) sc->step[A.par ^ 1] = st;
+    return;
+  }
   // plane slots: w at z in slot (z - z0 + 2) mod 5, m at z in (z - z0 + 1) mod 3
-  auto wslot = [&](int z) { return (z - z0 + 2) % 5; };
-  auto mslot = [&](int z) { return (z - z0 + 1) % 3; };
-  auto load_w = [&](int z) {
-    double* dst = Wp[wslot(z)];
-    for (int k = tid; k < WPL; k += NTH) {
-      const int lx = k % WX, ly = k / WX;
-      dst[k] = grid_val(win, g, x0 - 2 + lx, y0 - 2 + ly, z);
-    }
+  auto wslot = [&](int z) { return (z - C.z0 + 2) % 5; };
+  auto mslot = [&](int z) { return (z - C.z0 + 1) % 3; };
+  auto store_w = [&](int slot, const double (&v)[NW]) {
+#pragma unroll
+    for (int j = 0; j < NW; ++j)
+      if (tid + j * NTH < WPL) Wp[slot][tid + j * NTH] = v[j];
+  };
+#pragma unroll
+  for (int k = 0; k < 5; ++k) store_w(k, wr[k]);
+  block_sum(gd, red);   // its barrier also publishes the planes
+  const double gamma = gd[0], delta = gd[1];
+  double eps;
+  const bool stop = stop_at(sc, st.iter, gamma, eps);
+  double beta = 0.0, alpha = gamma / delta;
+  if (st.iter > 0) {
+    beta = gamma / st.gamma_prev;
+    alpha = gamma / (delta - beta * gamma / st.alpha_prev);
+  }
+  if (blockIdx.x == 0 && tid == 0) {
+    A.hist[st.iter] = eps;
+    if (st.iter == 0) sc->gamma0 = gamma;
+    if (stop) sc->step[A.par ^ 1] = {st.alpha_prev, st.gamma_prev, st.iter, 1};
+    else sc->step[A.par ^ 1] = {alpha, gamma, st.iter + 1, 0};
+  }
+  if (stop) return;
+  // the six neighbours of point c of plane b (row stride S), a below, d above
+  auto six_lds = [](const double* a, const double* b, const double* d, int c, int S) {
+    double s = b[c - 1];
+    s += b[c + 1];
+    s += b[c - S];
+    s += b[c + S];
+    s += a[c];
+    s += d[c];
+    return s;
   };
   // m = M^-1 w on the plane z (1-cell halo); 0 off the grid under Dirichlet
   auto comp_m = [&](int z) {
-    const double* wm = Wp[wslot(z - 1)];
-    const double* w0 = Wp[wslot(z)];
-    const double* wp = Wp[wslot(z + 1)];
+    const double *wm = Wp[wslot(z - 1)], *w0 = Wp[wslot(z)], *wp = Wp[wslot(z + 1)];
     double* dst = Mp[mslot(z)];
-    for (int k = tid; k < MPL; k += NTH) {
-      const int lx = k % MX, ly = k / MX;
-      const int X = x0 - 1 + lx, Y = y0 - 1 + ly;
-      const bool in = periodic || (X >= 0 && X < g.n0 && Y >= 0 && Y < g.n1 && z >= 0 && z < g.n2);
-      const int c = (lx + 1) + WX * (ly + 1);
-      double v = 0.0;
-      if (in) {
-        if (PC == RY_PC_STENCIL7) {
-          double s = w0[c - 1];
-          s += w0[c + 1];
-          s += w0[c - WX];
-          s += w0[c + WX];
-          s += wm[c];
-          s += wp[c];
-          v = (13.0 / 12.0) * w0[c] + (1.0 / 6.0) * s;
-        } else {
-          v = w0[c];
-        }
-      }
-      dst[k] = v;
+    const bool ok = C.inz(z);
+#pragma unroll
+    for (int j = 0; j < NM; ++j) {
+      const int k = tid + j * NTH;
+      if (k >= MPL) continue;
+      const int c = (k % MX + 1) + WX * (k / MX + 1);
+      const double v = PC == RY_PC_STENCIL7 ? (13.0 / 12.0) * w0[c] + (1.0 / 6.0) * six_lds(wm, w0, wp, c, WX) : w0[c];
+      dst[k] = ok && inm[j] ? v : 0.0;
     }
   };
-
-  load_w(z0 - 2);
-  load_w(z0 - 1);
-  load_w(z0);
-  load_w(z0 + 1);
+  comp_m(C.z0 - 1);
+  comp_m(C.z0);
+  comp_m(C.z0 + 1);
   __syncthreads();
-  comp_m(z0 - 1);
-  comp_m(z0);
-  double acc_g = 0.0, acc_d = 0.0;
-  const int X = x0 + tx, Y = y0 + ty;
-  const bool own = X < g.n0 && Y < g.n1;
-  const int64_t plane = int64_t(g.n0) * g.n1;
-  const int64_t col = int64_t(X) + int64_t(g.n0) * Y;
-  // The eight recurrence vectors are touched once per iteration: stream
-  // them with non-temporal loads and stores so that L2 keeps the w planes
-  // the neighbouring workgroups read as halo.
-  constexpr int NW = (WPL + NTH - 1) / NTH;
-  for (int z = z0; z < z1; ++z) {
-    double wr[NW];
-#pragma unroll
-    for (int j = 0; j < NW; ++j) {
-      const int k = tid + j * NTH;
-      if (k < WPL) wr[j] = grid_val(win, g, x0 - 2 + k % WX, y0 - 2 + k / WX, z + 2);
+  double acc[2] = {0.0, 0.0};
+  for (int z = C.z0; z < C.z1; ++z) {
+    const bool more = z + 1 < C.z1;
+    if (more) {
+      load_w(z + 3, wr[0]);
+      nxt = load_rec(z + 1);
     }
-#pragma unroll
-    for (int j = 0; j < NW; ++j) {
-      const int k = tid + j * NTH;
-      if (k < WPL) Wp[wslot(z + 2)][k] = wr[j];
-    }
-    __syncthreads();
-    comp_m(z + 1);
-    __syncthreads();
     if (own) {
-      const int64_t i = col + plane * z;
-      const double z_old = __builtin_nontemporal_load(A.z + i);
-      const double q_old = __builtin_nontemporal_load(A.q + i);
-      const double s_old = __builtin_nontemporal_load(A.s + i);
-      const double p_old = __builtin_nontemporal_load(A.p + i);
-      const double u_old = __builtin_nontemporal_load(A.u + i);
-      const double x_old = __builtin_nontemporal_load(A.x + i);
-      const double r_old = __builtin_nontemporal_load(A.r + i);
-      const double* mm = Mp[mslot(z - 1)];
+      const int64_t i = col + C.plane * z;
       const double* m0 = Mp[mslot(z)];
-      const double* mp = Mp[mslot(z + 1)];
       const int c = (tx + 1) + MX * (ty + 1);
-      double s = m0[c - 1];
-      s += m0[c + 1];
-      s += m0[c - MX];
-      s += m0[c + MX];
-      s += mm[c];
-      s += mp[c];
       const double mv = m0[c];
-      const double nv = 6.0 * mv - s;                         // n_i = A m_i
+      const double nv = 6.0 * mv - six_lds(Mp[mslot(z - 1)], m0, Mp[mslot(z + 1)], c, MX);   // n_i = A m_i
       const double wv = Wp[wslot(z)][(tx + 2) + WX * (ty + 2)];
-      const double zz = nv + beta * z_old;
-      const double qq = mv + beta * q_old;
-      const double ss = wv + beta * s_old;
-      const double pp = u_old + beta * p_old;
-      const double xx = x_old + alpha * pp;
-      const double rr = r_old - alpha * ss;
-      const double uu = u_old - alpha * qq;
+      const double zz = nv + beta * rec.z;
+      const double qq = mv + beta * rec.q;
+      const double ss = wv + beta * rec.s;
+      const double pp = rec.u + beta * rec.p;
+      const double rr = rec.r - alpha * ss;
+      const double uu = rec.u - alpha * qq;
       const double ww = wv - alpha * zz;
-      __builtin_nontemporal_store(zz, A.z + i);
-      __builtin_nontemporal_store(qq, A.q + i);
-      __builtin_nontemporal_store(ss, A.s + i);
-      __builtin_nontemporal_store(pp, A.p + i);
-      __builtin_nontemporal_store(xx, A.x + i);
-      __builtin_nontemporal_store(rr, A.r + i);
-      __builtin_nontemporal_store(uu, A.u + i);
-      __builtin_nontemporal_store(ww, wout + i);
-      acc_g += rr * uu;
-      acc_d += ww * uu;
+      A.z[i] = zz;
+      A.q[i] = qq;
+      A.s[i] = ss;
+      A.p[i] = pp;
+      A.x[i] = rec.x + alpha * pp;
+      A.r[i] = rr;
+      A.u[i] = uu;
+      wout[i] = ww;
+      acc[0] += rr * uu;
+      acc[1] += ww * uu;
+    }
+    if (more) {
+      store_w(wslot(z + 3), wr[0]);
+      __syncthreads();
+      comp_m(z + 2);
+      __syncthreads();
+      rec = nxt;
     }
   }
-  block_partials(acc_g, acc_d, A.part);
+  block_sum(acc, red);   // the barrier after comp_m separates it from the first sum
+  if (tid == 0) {
+    part_out[blockIdx.x] = acc[0];
+    part_out[nb + blockIdx.x] = acc[1];
+  }
 }
 
 // ---------------------------------------------------------------------------
-// Scalar step: gamma_i, delta_i from the partials; eps_i; alpha_i, beta_i.
+// The two sweeps of the large problems.  Bound: HBM (256^3: direction 96 us
+// for 403 MB, update 134 us for 671 MB: 4.2 and 5.0 TB/s).  The direction
+// sweep marches down, so that it starts on the planes the update sweep left
+// in the caches (1.5% at 256^3).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void ppcg_finalize_kernel(Scalars* sc, const double* __restrict__ part,
-                                                             int npart, double* hist) {
-  if (sc->done) return;
-  __shared__ double sg[1024], sd[1024];
-  double a = 0.0, b = 0.0;
-  for (int k = threadIdx.x; k < npart; k += 1024) {
-    a += part[k];
-    b += part[npart + k];
-  }
-  sg[threadIdx.x] = a;
-  sd[threadIdx.x] = b;
-  __syncthreads();
-  for (int h = 512; h > 0; h >>= 1) {
-    if (int(threadIdx.x) < h) {
-      sg[threadIdx.x] += sg[threadIdx.x + h];
-      sd[threadIdx.x] += sd[threadIdx.x + h];
+// gamma_i, the stopping test and beta_i; p_i = M^-1 r_i + beta_i p_{i-1} on
+// the tile and its one-cell halo; partials of p_i.(A p_i).
+template <int PC>
+__global__ __launch_bounds__(LargeTile::NT) void cg_direction_kernel(CgArgs A) {
+  using T = LargeTile;
+  Scalars* sc = A.sc;
+  const Scalars::Step st = sc->step[0];
+  if (st.done) return;
+  __shared__ double Rp[2][T::PL], Pp[2][T::PL];
+  __shared__ double red[1][T::NWV];
+  const Point<T, true> P(A.g, A.cz);
+  const double* __restrict__ r = A.r[st.iter & 1];
+  const double* __restrict__ pold = A.p[st.iter & 1];
+  double* __restrict__ pnew = A.p[(st.iter & 1) ^ 1];
+  double rm = P.load2(r, P.z0 - 2), r0 = P.load2(r, P.z0 - 1), r1 = P.load2(r, P.z0);
+  double rq[2] = {P.load2(r, P.z0 + 1), P.load2(r, P.z0 + 2)};
+  double pq[2] = {P.load1(pold, P.z0 - 1), P.load1(pold, P.z0)};
+  // the scalar step, by the first wavefront
+  Rp[0][P.c] = r0;
+  __shared__ double s_beta;
+  __shared__ int s_stop;
+  if (threadIdx.x < 64) {
+    const double gamma = wave_total(A.part_g, gridDim.x);
+    double eps;
+    const bool stop = stop_at(sc, st.iter, gamma, eps);
+    if (threadIdx.x == 0) {
+      s_beta = st.iter > 0 ? gamma / st.gamma_prev : 0.0;
+      s_stop = stop;
+      if (blockIdx.x == 0) {
+        A.hist[st.iter] = eps;
+        if (st.iter == 0) sc->gamma0 = gamma;
+        sc->dir = {gamma, st.iter, stop ? 1 : 0};
+      }
     }
-    __syncthreads();
   }
-  if (threadIdx.x != 0) return;
-  const double gamma = sg[0], delta = sd[0];
-  const int i = sc->iter;
-  if (i == 0) sc->gamma0 = gamma;
-  const double g0 = (i == 0) ? gamma : sc->gamma0;
-  const double eps = (g0 > 0.0 && gamma > 0.0) ? sqrt(gamma / g0) : 0.0;
-  hist[i] = eps;
-  if (eps <= sc->eps_target || i >= sc->max_iter || i >= RY_POISSON_HIST - 1) {
-    sc->done = 1;
+  __syncthreads();
+  if (s_stop) return;
+  const double beta = s_beta;
+  double pm = 0.0, p0 = 0.0;
+  double acc[1] = {0.0};
+  // p at plane z, then A p at plane z - 1; r holds z - 1 .. z + 1
+  auto step = [&](int z, int b, double& rnext, double& pz) {
+    if (z >= P.z0) {
+      Rp[b][P.c] = r0;
+      Pp[b ^ 1][P.c] = p0;
+      __syncthreads();
+    }
+    const double u = PC == RY_PC_STENCIL7 ? (13.0 / 12.0) * r0 + (1.0 / 6.0) * six<T>(Rp[b], P.c, rm, r1) : r0;
+    const double p1 = (P.in && P.inz(z)) ? u + beta * pz : 0.0;
+    pz = P.load1(pold, z + 2);
+    if (P.own && z >= P.z0 && z < P.z1) pnew[P.cell(z)] = p1;
+    const double ap = 6.0 * p0 - six<T>(Pp[b ^ 1], P.c, pm, p1);
+    acc[0] += (P.own && z > P.z0) ? p0 * ap : 0.0;
+    rm = r0;
+    r0 = r1;
+    r1 = rnext;
+    rnext = P.load2(r, z + 4);
+    pm = p0;
+    p0 = p1;
+  };
+  for (int z = P.z0 - 1; z <= P.z1; z += 2) {
+    step(z, 0, rq[0], pq[0]);
+    if (z + 1 <= P.z1) step(z + 1, 1, rq[1], pq[1]);
+  }
+  block_sum(acc, red);
+  if (threadIdx.x == 0) A.part_d[blockIdx.x] = acc[0];
+}
+
+// alpha_i; r_{i+1} = r_i - alpha_i A p_i on the tile and its one-cell halo,
+// x_{i+1} = x_i + alpha_i p_i; partials of gamma_{i+1}.
+template <int PC>
+__global__ __launch_bounds__(LargeTile::NT) void cg_update_kernel(CgArgs A) {
+  using T = LargeTile;
+  Scalars* sc = A.sc;
+  const Scalars::Dir dir = sc->dir;
+  if (dir.done) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) sc->step[0].done = 1;
     return;
   }
-  double alpha, beta;
-  if (i > 0) {
-    beta = gamma / sc->gamma_prev;
-    alpha = gamma / (delta - beta * gamma / sc->alpha_prev);
-  } else {
-    beta = 0.0;
-    alpha = gamma / delta;
+  __shared__ double Pp[2][T::PL], Rp[2][T::PL];
+  __shared__ double red[1][T::NWV];
+  const Point<T> P(A.g, A.cz);
+  const double* __restrict__ p = A.p[(dir.iter & 1) ^ 1];
+  const double* __restrict__ rold = A.r[dir.iter & 1];
+  double* __restrict__ rnew = A.r[(dir.iter & 1) ^ 1];
+  double pm = P.load2(p, P.z0 - 2), p0 = P.load2(p, P.z0 - 1), p1 = P.load2(p, P.z0);
+  double pq[2] = {P.load2(p, P.z0 + 1), P.load2(p, P.z0 + 2)};
+  double rq[2] = {P.load1(rold, P.z0 - 1), P.load1(rold, P.z0)};
+  auto load_x = [&](int z) { return A.x[P.cell(z)]; };
+  double xq[2] = {0.0, 0.0};   // x is used one plane behind r: the first two planes only load it
+  // the scalar step, by the first wavefront
+  Pp[0][P.c] = p0;
+  __shared__ double s_alpha;
+  if (threadIdx.x < 64) {
+    const double a = dir.gamma / wave_total(A.part_d, gridDim.x);
+    if (threadIdx.x == 0) {
+      s_alpha = a;
+      if (blockIdx.x == 0) sc->step[0] = {a, dir.gamma, dir.iter + 1, 0};
+    }
   }
-  sc->alpha = alpha;
-  sc->beta = beta;
-  sc->alpha_prev = alpha;
-  sc->gamma_prev = gamma;
-  sc->src = i & 1;
-  sc->iter = i + 1;
+  __syncthreads();
+  const double alpha = s_alpha;
+  double rm = 0.0, r0 = 0.0;
+  double acc[1] = {0.0};
+  // r at plane z, then everything else at plane z - 1; p holds z - 1 .. z + 1
+  auto step = [&](int z, int b, double& pnext, double& rz, double& xz) {
+    if (z >= P.z0) {
+      Pp[b][P.c] = p0;
+      Rp[b ^ 1][P.c] = r0;
+      __syncthreads();
+    }
+    double r1 = rz - alpha * (6.0 * p0 - six<T>(Pp[b], P.c, pm, p1));
+    r1 = (P.in && P.inz(z)) ? r1 : 0.0;
+    rz = P.load1(rold, z + 2);
+    const double u = PC == RY_PC_STENCIL7 ? (13.0 / 12.0) * r0 + (1.0 / 6.0) * six<T>(Rp[b ^ 1], P.c, rm, r1) : r0;
+    if (P.own && z > P.z0) {
+      const int64_t i = P.cell(z - 1);
+      rnew[i] = r0;
+      A.x[i] = xz + alpha * pm;
+      acc[0] += r0 * u;
+    }
+    xz = load_x(z + 1);
+    pm = p0;
+    p0 = p1;
+    p1 = pnext;
+    pnext = P.load2(p, z + 4);
+    rm = r0;
+    r0 = r1;
+  };
+  for (int z = P.z0 - 1; z <= P.z1; z += 2) {
+    step(z, 0, pq[0], rq[0], xq[0]);
+    if (z + 1 <= P.z1) step(z + 1, 1, pq[1], rq[1], xq[1]);
+  }
+  block_sum(acc, red);
+  if (threadIdx.x == 0) A.part_g[blockIdx.x] = acc[0];
 }
 
-// (Re)arm the stopping rule: absolute max_iter, or relative to the current i.
-__global__ void ppcg_arm_kernel(Scalars* sc, double eps, int32_t max_iter, int32_t relative) {
-  sc->done = 0;
+// (Re)arm the stopping rule: absolute max_iter, or relative to the current
+// iterate's index (held by step[slot]).
+__global__ void ppcg_arm_kernel(Scalars* sc, double eps, int32_t max_iter, int32_t relative, int32_t slot) {
+  sc->step[0].done = sc->step[1].done = sc->dir.done = 0;
   sc->eps_target = eps;
-  sc->max_iter = relative ? sc->iter + max_iter : max_iter;
+  sc->max_iter = relative ? sc->step[slot].iter + max_iter : max_iter;
 }
 
 __global__ void ppcg_reset_kernel(Scalars* sc) {
-  sc->gamma0 = sc->alpha = sc->beta = sc->alpha_prev = sc->gamma_prev = 0.0;
+  *sc = Scalars{};
   sc->eps_target = -1.0;
-  sc->iter = 0;
-  sc->max_iter = 0;
-  sc->done = 1;
-  sc->src = 0;
+  sc->step[0].done = sc->step[1].done = sc->dir.done = 1;
 }
 
 // ---------------------------------------------------------------------------
-// Start-up sweeps (once per solve): r = b - A x, u = M^-1 r, w = A u with the
-// partials of r.u and w.u laid out like the iteration kernel's.
+// Start-up sweeps (once per solve), and the operators applied to a whole
+// vector (the two-sweep form's vectors on request).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ double nb_sum(const double* v, const Grid& g, int X, int Y, int Z) {
   double s = grid_val(v, g, X - 1, Y, Z);
@@ -331,38 +647,93 @@ __device__ __forceinline__ double nb_sum(const double* v, const Grid& g, int X, 
   s += grid_val(v, g, X, Y, Z + 1);
   return s;
 }
+__device__ __forceinline__ void cell_of(const Grid& g, int64_t i, int& X, int& Y, int& Z) {
+  const uint32_t c = uint32_t(i), row = c / uint32_t(g.n0);   // fewer than 2^31 cells
+  X = int(c - row * uint32_t(g.n0));
+  Z = int(row / uint32_t(g.n1));
+  Y = int(row) - Z * g.n1;
+}
 
-__global__ __launch_bounds__(256) void residual_kernel(Grid g, const double* __restrict__ b,
-                                                       const double* __restrict__ x, double* __restrict__ r) {
+// r = b - A x (zero_x: from x = 0, which is stored), and zeros in the
+// vectors of `clear`.  b may be one of them: each cell's b is read by the
+// thread that clears it.
+struct ClearList {
+  double* v[4];
+};
+__global__ __launch_bounds__(256) void residual_kernel(Grid g, const double* b, double* __restrict__ x, int zero_x,
+                                                       double* __restrict__ r, ClearList clear) {
   const int64_t N = int64_t(g.n0) * g.n1 * g.n2;
   for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < N; i += int64_t(gridDim.x) * blockDim.x) {
-    const int X = int(i % g.n0), Y = int((i / g.n0) % g.n1), Z = int(i / (int64_t(g.n0) * g.n1));
-    r[i] = b[i] - (6.0 * x[i] - nb_sum(x, g, X, Y, Z));
+    const double bv = b[i];
+    double rv = bv;
+    if (zero_x) {
+      x[i] = 0.0;
+    } else {
+      int X, Y, Z;
+      cell_of(g, i, X, Y, Z);
+      rv = bv - (6.0 * x[i] - nb_sum(x, g, X, Y, Z));
+    }
+    r[i] = rv;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (clear.v[k]) clear.v[k][i] = 0.0;
   }
+}
+
+__device__ __forceinline__ double apply_m(const double* r, const Grid& g, int pc, int64_t i) {
+  if (pc != RY_PC_STENCIL7) return r[i];
+  int X, Y, Z;
+  cell_of(g, i, X, Y, Z);
+  return (13.0 / 12.0) * r[i] + (1.0 / 6.0) * nb_sum(r, g, X, Y, Z);
+}
+__device__ __forceinline__ double apply_a(const double* u, const Grid& g, int64_t i) {
+  int X, Y, Z;
+  cell_of(g, i, X, Y, Z);
+  return 6.0 * u[i] - nb_sum(u, g, X, Y, Z);
 }
 
 __global__ __launch_bounds__(256) void minv_kernel(Grid g, int pc, const double* __restrict__ r,
                                                    double* __restrict__ u) {
   const int64_t N = int64_t(g.n0) * g.n1 * g.n2;
-  for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < N; i += int64_t(gridDim.x) * blockDim.x) {
-    const int X = int(i % g.n0), Y = int((i / g.n0) % g.n1), Z = int(i / (int64_t(g.n0) * g.n1));
-    u[i] = (pc == RY_PC_STENCIL7) ? (13.0 / 12.0) * r[i] + (1.0 / 6.0) * nb_sum(r, g, X, Y, Z) : r[i];
-  }
+  for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < N; i += int64_t(gridDim.x) * blockDim.x)
+    u[i] = apply_m(r, g, pc, i);
 }
 
+__global__ __launch_bounds__(256) void apply_a_kernel(Grid g, const double* __restrict__ u, double* __restrict__ w) {
+  const int64_t N = int64_t(g.n0) * g.n1 * g.n2;
+  for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < N; i += int64_t(gridDim.x) * blockDim.x)
+    w[i] = apply_a(u, g, i);
+}
+
+// w = A u and the partials of r.u and w.u (pipelined form).
 __global__ __launch_bounds__(NTH) void apply_a_dots_kernel(Grid g, const double* __restrict__ r,
                                                            const double* __restrict__ u, double* __restrict__ w,
                                                            double* part) {
+  __shared__ double red[2][NTH / 64];
   const int64_t N = int64_t(g.n0) * g.n1 * g.n2;
-  double a = 0.0, b = 0.0;
+  double ab[2] = {0.0, 0.0};
   for (int64_t i = blockIdx.x * int64_t(NTH) + threadIdx.x; i < N; i += int64_t(gridDim.x) * NTH) {
-    const int X = int(i % g.n0), Y = int((i / g.n0) % g.n1), Z = int(i / (int64_t(g.n0) * g.n1));
-    const double wv = 6.0 * u[i] - nb_sum(u, g, X, Y, Z);
+    const double wv = apply_a(u, g, i);
     w[i] = wv;
-    a += r[i] * u[i];
-    b += wv * u[i];
+    ab[0] += r[i] * u[i];
+    ab[1] += wv * u[i];
   }
-  block_partials(a, b, part);
+  block_sum(ab, red);
+  if (threadIdx.x == 0) {
+    part[blockIdx.x] = ab[0];
+    part[gridDim.x + blockIdx.x] = ab[1];
+  }
+}
+
+// Partials of r.(M^-1 r) (two-sweep form).
+__global__ __launch_bounds__(NTH) void gamma_kernel(Grid g, int pc, const double* __restrict__ r, double* part) {
+  __shared__ double red[1][NTH / 64];
+  const int64_t N = int64_t(g.n0) * g.n1 * g.n2;
+  double a[1] = {0.0};
+  for (int64_t i = blockIdx.x * int64_t(NTH) + threadIdx.x; i < N; i += int64_t(gridDim.x) * NTH)
+    a[0] += r[i] * apply_m(r, g, pc, i);
+  block_sum(a, red);
+  if (threadIdx.x == 0) part[blockIdx.x] = a[0];
 }
 
 }  // namespace ryp
@@ -379,15 +750,16 @@ struct ry_poisson {
   hipStream_t stream = nullptr;
   bool own_stream = false;
   std::vector<void*> allocs;
-  double* v[NVEC] = {};        // x r u w0 w1 z q s p
-  double* part = nullptr;
+  bool two_sweep = false;
+  double* v[NVEC] = {};        // x r u w0 w1 z q s p; two-sweep: x r0 r1 p0 p1
+  double* part = nullptr;      // pipelined: [2][2][nblk]; two-sweep: [2][nblk] (gamma, p.Ap)
   double* hist = nullptr;
   Scalars* sc = nullptr;
   int32_t* h_done = nullptr;   // pinned
   int nblk = 0, cz = 0;
   bool ready = false;          // set_rhs done
-  int64_t iter_hi = 0;         // upper bound of the device iteration index
-  hipGraphExec_t graph = nullptr;
+  int64_t iter = 0;            // the device's iteration index (once the stream's work is done)
+  hipGraphExec_t graph[2] = {};   // by parity of the first iteration's index (two-sweep: [0])
   bool timing = false;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> ev;
   int64_t t_launches = 0;
@@ -430,8 +802,10 @@ void pfree_all(ry_poisson* p) {
     else if (!p->cfg.dev_alloc) hipFree(a);
   }
   p->allocs.clear();
-  if (p->graph) hipGraphExecDestroy(p->graph);
-  p->graph = nullptr;
+  for (auto& gr : p->graph) {
+    if (gr) hipGraphExecDestroy(gr);
+    gr = nullptr;
+  }
   for (auto& e : p->ev) {
     hipEventDestroy(e.first);
     hipEventDestroy(e.second);
@@ -441,7 +815,7 @@ void pfree_all(ry_poisson* p) {
   p->h_done = nullptr;
 }
 
-IterArgs iter_args(ry_poisson* p) {
+IterArgs iter_args(ry_poisson* p, int par) {
   IterArgs a;
   a.g = p->g;
   a.x = p->v[0];
@@ -454,19 +828,38 @@ IterArgs iter_args(ry_poisson* p) {
   a.s = p->v[7];
   a.p = p->v[8];
   a.sc = p->sc;
+  a.hist = p->hist;
   a.part = p->part;
+  a.cz = p->cz;
+  a.par = par;
+  return a;
+}
+
+CgArgs cg_args(ry_poisson* p) {
+  CgArgs a;
+  a.g = p->g;
+  a.x = p->v[0];
+  a.r[0] = p->v[1];
+  a.r[1] = p->v[2];
+  a.p[0] = p->v[3];
+  a.p[1] = p->v[4];
+  a.sc = p->sc;
+  a.hist = p->hist;
+  a.part_g = p->part;
+  a.part_d = p->part + p->nblk;
   a.cz = p->cz;
   return a;
 }
 
-// One finalize (+ the iteration kernel unless `finalize_only`).
-ry_status launch_iteration(ry_poisson* p, bool finalize_only = false) {
-  hipLaunchKernelGGL(ppcg_finalize_kernel, dim3(1), dim3(1024), 0, p->stream, p->sc, p->part, p->nblk, p->hist);
-  if (finalize_only) {
-    PCHK(p, hipGetLastError());
-    return RY_OK;
-  }
-  if (p->timing) {
+// The slot of Scalars::step that the next iteration reads.
+int step_slot(const ry_poisson* p) { return p->two_sweep ? 0 : int(p->iter & 1); }
+
+// The iteration of parity `par` (which first tests the iterate it starts
+// from and does nothing more when the solve stops there); `timed`: between
+// two events.
+ry_status launch_iteration(ry_poisson* p, int par, bool timed) {
+  const dim3 grid(p->nblk), block(p->two_sweep ? LargeTile::NT : NTH);
+  if (timed) {
     hipEvent_t a, b;
     // timing-only events: no system-scope fence (cache write-back) on recording
     PCHK(p, hipEventCreateWithFlags(&a, hipEventDisableSystemFence));
@@ -474,20 +867,33 @@ ry_status launch_iteration(ry_poisson* p, bool finalize_only = false) {
     PCHK(p, hipEventRecord(a, p->stream));
     p->ev.push_back({a, b});
   }
-  if (p->cfg.precond == RY_PC_STENCIL7)
-    hipLaunchKernelGGL(ppcg_iterate_kernel<RY_PC_STENCIL7>, dim3(p->nblk), dim3(NTH), 0, p->stream, iter_args(p));
-  else
-    hipLaunchKernelGGL(ppcg_iterate_kernel<RY_PC_NONE>, dim3(p->nblk), dim3(NTH), 0, p->stream, iter_args(p));
-  if (p->timing) PCHK(p, hipEventRecord(p->ev.back().second, p->stream));
+  const bool pc = p->cfg.precond == RY_PC_STENCIL7;
+  if (p->two_sweep) {
+    const CgArgs a = cg_args(p);
+    if (pc) {
+      hipLaunchKernelGGL(cg_direction_kernel<RY_PC_STENCIL7>, grid, block, 0, p->stream, a);
+      hipLaunchKernelGGL(cg_update_kernel<RY_PC_STENCIL7>, grid, block, 0, p->stream, a);
+    } else {
+      hipLaunchKernelGGL(cg_direction_kernel<RY_PC_NONE>, grid, block, 0, p->stream, a);
+      hipLaunchKernelGGL(cg_update_kernel<RY_PC_NONE>, grid, block, 0, p->stream, a);
+    }
+  } else {
+    const IterArgs a = iter_args(p, par);
+    if (pc) hipLaunchKernelGGL(ppcg_iterate_kernel<RY_PC_STENCIL7>, grid, block, 0, p->stream, a);
+    else hipLaunchKernelGGL(ppcg_iterate_kernel<RY_PC_NONE>, grid, block, 0, p->stream, a);
+  }
+  if (timed) PCHK(p, hipEventRecord(p->ev.back().second, p->stream));
   PCHK(p, hipGetLastError());
   return RY_OK;
 }
 
-ry_status ensure_graph(ry_poisson* p) {
-  if (p->graph) return RY_OK;
+// BATCH iterations as one graph, the first one's index of parity `par`.
+ry_status ensure_graph(ry_poisson* p, int par) {
+  hipGraphExec_t& ge = p->graph[par];
+  if (ge) return RY_OK;
   PCHK(p, hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal));
   ry_status s = RY_OK;
-  for (int k = 0; k < BATCH && s == RY_OK; ++k) s = launch_iteration(p);
+  for (int k = 0; k < BATCH && s == RY_OK; ++k) s = launch_iteration(p, (par + k) & 1, false);
   hipGraph_t gr = nullptr;
   const hipError_t e = hipStreamEndCapture(p->stream, &gr);
   if (s) {
@@ -495,9 +901,12 @@ ry_status ensure_graph(ry_poisson* p) {
     return s;
   }
   if (e != hipSuccess) return pfail(p, RY_EHIP, "graph capture: %s", hipGetErrorString(e));
-  const hipError_t e2 = hipGraphInstantiate(&p->graph, gr, nullptr, nullptr, 0);
+  const hipError_t e2 = hipGraphInstantiate(&ge, gr, nullptr, nullptr, 0);
   hipGraphDestroy(gr);
-  if (e2 != hipSuccess) return pfail(p, RY_EHIP, "graph instantiate: %s", hipGetErrorString(e2));
+  if (e2 != hipSuccess) {
+    ge = nullptr;
+    return pfail(p, RY_EHIP, "graph instantiate: %s", hipGetErrorString(e2));
+  }
   return RY_OK;
 }
 
@@ -558,16 +967,18 @@ ry_status ry_poisson_create(const ry_poisson_config* cfg, ry_poisson** out) {
     p->own_stream = true;
   }
   // z chunks: enough workgroups to fill 256 CUs several times over
-  const int gx = (cfg->n[0] + TX - 1) / TX, gy = (cfg->n[1] + TY - 1) / TY;
-  int nch = (2048 + gx * gy - 1) / (gx * gy);
+  p->two_sweep = N >= kTwoSweepCells;
+  const int tx = p->two_sweep ? LargeTile::TX : SmallTile::TX, ty = p->two_sweep ? LargeTile::TY : SmallTile::TY;
+  const int gx = (cfg->n[0] + tx - 1) / tx, gy = (cfg->n[1] + ty - 1) / ty;
+  int64_t nch = (p->two_sweep ? kTargetLarge : kTargetSmall) / (int64_t(gx) * gy);
   if (nch > cfg->n[2]) nch = cfg->n[2];
   if (nch < 1) nch = 1;
-  p->cz = (cfg->n[2] + nch - 1) / nch;
+  p->cz = int32_t((cfg->n[2] + nch - 1) / nch);
   nch = (cfg->n[2] + p->cz - 1) / p->cz;
-  p->nblk = gx * gy * nch;
+  p->nblk = int(gx * gy * nch);
   bool ok = true;
-  for (int k = 0; k < NVEC && ok; ++k) ok = (p->v[k] = static_cast<double*>(palloc(p, sizeof(double) * N))) != nullptr;
-  ok = ok && (p->part = static_cast<double*>(palloc(p, sizeof(double) * 2 * p->nblk))) != nullptr;
+  for (int k = 0; k < (p->two_sweep ? 5 : NVEC) && ok; ++k) ok = (p->v[k] = static_cast<double*>(palloc(p, sizeof(double) * N))) != nullptr;
+  ok = ok && (p->part = static_cast<double*>(palloc(p, sizeof(double) * 4 * p->nblk))) != nullptr;
   ok = ok && (p->hist = static_cast<double*>(palloc(p, sizeof(double) * RY_POISSON_HIST))) != nullptr;
   ok = ok && (p->sc = static_cast<Scalars*>(palloc(p, sizeof(Scalars)))) != nullptr;
   if (ok && hipHostMalloc((void**)&p->h_done, sizeof(int32_t)) != hipSuccess) {
@@ -603,21 +1014,28 @@ ry_status ry_poisson_set_rhs(ry_poisson* p, const double* b, const double* x0) {
   RY_ABI_TRY
   if (!p || !b) return RY_EINVAL;
   const size_t bytes = sizeof(double) * size_t(p->N);
-  double *x = p->v[0], *r = p->v[1], *u = p->v[2], *w0 = p->v[3], *z = p->v[5];
-  // b is staged in z, which is cleared once r has been formed
-  PCHK(p, hipMemcpyAsync(z, b, bytes, hipMemcpyHostToDevice, p->stream));
+  // b is staged in a vector that holds nothing yet: z (cleared once r has
+  // been formed) or the second direction buffer (the first iteration writes it)
+  double *x = p->v[0], *r = p->v[1], *stage = p->v[p->two_sweep ? 4 : 5];
+  ClearList clear{};
+  if (p->two_sweep) clear.v[0] = p->v[3];
+  else
+    for (int k = 0; k < 4; ++k) clear.v[k] = p->v[5 + k];
+  PCHK(p, hipMemcpyAsync(stage, b, bytes, hipMemcpyHostToDevice, p->stream));
   if (x0) PCHK(p, hipMemcpyAsync(x, x0, bytes, hipMemcpyHostToDevice, p->stream));
-  else PCHK(p, hipMemsetAsync(x, 0, bytes, p->stream));
   const int blocks = int(std::min<int64_t>((p->N + 255) / 256, 8192));
-  hipLaunchKernelGGL(residual_kernel, dim3(blocks), dim3(256), 0, p->stream, p->g, z, x, r);
-  hipLaunchKernelGGL(minv_kernel, dim3(blocks), dim3(256), 0, p->stream, p->g, p->cfg.precond, r, u);
-  hipLaunchKernelGGL(apply_a_dots_kernel, dim3(p->nblk), dim3(NTH), 0, p->stream, p->g, r, u, w0, p->part);
-  PCHK(p, hipGetLastError());
-  for (int k = 5; k < NVEC; ++k) PCHK(p, hipMemsetAsync(p->v[k], 0, bytes, p->stream));
+  hipLaunchKernelGGL(residual_kernel, dim3(blocks), dim3(256), 0, p->stream, p->g, stage, x, x0 ? 0 : 1, r, clear);
+  if (p->two_sweep) {
+    hipLaunchKernelGGL(gamma_kernel, dim3(p->nblk), dim3(NTH), 0, p->stream, p->g, p->cfg.precond, r, p->part);
+  } else {
+    double *u = p->v[2], *w0 = p->v[3];
+    hipLaunchKernelGGL(minv_kernel, dim3(blocks), dim3(256), 0, p->stream, p->g, p->cfg.precond, r, u);
+    hipLaunchKernelGGL(apply_a_dots_kernel, dim3(p->nblk), dim3(NTH), 0, p->stream, p->g, r, u, w0, p->part);
+  }
   hipLaunchKernelGGL(ppcg_reset_kernel, dim3(1), dim3(1), 0, p->stream, p->sc);
   PCHK(p, hipGetLastError());
   p->ready = true;
-  p->iter_hi = 0;
+  p->iter = 0;
   return RY_OK;
   RY_ABI_CATCH
 }
@@ -627,31 +1045,36 @@ ry_status ry_poisson_solve(ry_poisson* p, double eps, int32_t max_iter, int32_t*
   if (!p) return RY_EINVAL;
   if (!p->ready) return pfail(p, RY_ESTATE, "ry_poisson_solve before ry_poisson_set_rhs");
   if (max_iter < 0 || max_iter > RY_POISSON_HIST - 1 || std::isnan(eps)) return RY_EINVAL;
-  hipLaunchKernelGGL(ppcg_arm_kernel, dim3(1), dim3(1), 0, p->stream, p->sc, eps, max_iter, 0);
+  hipLaunchKernelGGL(ppcg_arm_kernel, dim3(1), dim3(1), 0, p->stream, p->sc, eps, max_iter, 0,
+                     step_slot(p));
   PCHK(p, hipGetLastError());
+  const int par = step_slot(p);
   if (!p->timing) {
-    ry_status s = ensure_graph(p);
+    ry_status s = ensure_graph(p, par);
     if (s) return s;
   }
+  // after a batch (an even number of iterations) the newest record is in the
+  // slot it started from
+  const int32_t* done = p->two_sweep ? &p->sc->dir.done : &p->sc->step[par].done;
   const int64_t batches = int64_t(max_iter) / BATCH + 2;
   for (int64_t k = 0; k < batches; ++k) {
     if (p->timing) {
       for (int j = 0; j < BATCH; ++j) {
-        ry_status s = launch_iteration(p);
+        ry_status s = launch_iteration(p, (par + j) & 1, true);
         if (s) return s;
       }
     } else {
-      PCHK(p, hipGraphLaunch(p->graph, p->stream));
+      PCHK(p, hipGraphLaunch(p->graph[par], p->stream));
     }
-    PCHK(p, hipMemcpyAsync(p->h_done, &p->sc->done, sizeof(int32_t), hipMemcpyDeviceToHost, p->stream));
+    PCHK(p, hipMemcpyAsync(p->h_done, done, sizeof(int32_t), hipMemcpyDeviceToHost, p->stream));
     PCHK(p, hipStreamSynchronize(p->stream));
     if (*p->h_done) break;
   }
   Scalars s{};
   PCHK(p, hipMemcpy(&s, p->sc, sizeof s, hipMemcpyDeviceToHost));
-  if (!s.done) return pfail(p, RY_ESTATE, "solver did not stop");
-  p->iter_hi = s.iter;
-  if (n_iter) *n_iter = s.iter;
+  if (!*p->h_done) return pfail(p, RY_ESTATE, "solver did not stop");
+  p->iter = s.step[par].iter;
+  if (n_iter) *n_iter = int32_t(p->iter);
   if (p->timing) collect_times(p);
   return RY_OK;
   RY_ABI_CATCH
@@ -661,22 +1084,24 @@ ry_status ry_poisson_iterate(ry_poisson* p, int32_t n) {
   RY_ABI_TRY
   if (!p || n < 0) return RY_EINVAL;
   if (!p->ready) return pfail(p, RY_ESTATE, "ry_poisson_iterate before ry_poisson_set_rhs");
-  if (p->iter_hi + n > RY_POISSON_HIST - 1) return pfail(p, RY_EINVAL, "iteration history full");
+  if (p->iter + n > RY_POISSON_HIST - 1) return pfail(p, RY_EINVAL, "iteration history full");
   if (n == 0) return RY_OK;
-  hipLaunchKernelGGL(ppcg_arm_kernel, dim3(1), dim3(1), 0, p->stream, p->sc, -1.0, n, 1);
+  hipLaunchKernelGGL(ppcg_arm_kernel, dim3(1), dim3(1), 0, p->stream, p->sc, -1.0, n, 1,
+                     step_slot(p));
   PCHK(p, hipGetLastError());
-  // n iterations plus the finalize that records eps of the last iterate
+  const int par = step_slot(p);
+  // n iterations plus one that only records eps of the last iterate
   if (p->timing) {
     for (int j = 0; j <= n; ++j) {
-      ry_status s = launch_iteration(p, j == n);
+      ry_status s = launch_iteration(p, (par + j) & 1, j < n);
       if (s) return s;
     }
   } else {
-    ry_status s = ensure_graph(p);
+    ry_status s = ensure_graph(p, par);
     if (s) return s;
-    for (int j = 0; j <= n; j += BATCH) PCHK(p, hipGraphLaunch(p->graph, p->stream));
+    for (int j = 0; j <= n; j += BATCH) PCHK(p, hipGraphLaunch(p->graph[par], p->stream));
   }
-  p->iter_hi += n;
+  p->iter += n;
   return RY_OK;
   RY_ABI_CATCH
 }
@@ -684,10 +1109,8 @@ ry_status ry_poisson_iterate(ry_poisson* p, int32_t n) {
 ry_status ry_poisson_eps_history(ry_poisson* p, double* eps, int32_t cap, int32_t* n) {
   RY_ABI_TRY
   if (!p || !eps || cap < 0) return RY_EINVAL;
-  Scalars s{};
   PCHK(p, hipStreamSynchronize(p->stream));
-  PCHK(p, hipMemcpy(&s, p->sc, sizeof s, hipMemcpyDeviceToHost));
-  const int32_t k = std::min<int32_t>(s.iter + 1, cap);
+  const int32_t k = int32_t(std::min<int64_t>(p->iter + 1, cap));
   if (k > 0) PCHK(p, hipMemcpy(eps, p->hist, sizeof(double) * k, hipMemcpyDeviceToHost));
   if (n) *n = k;
   return RY_OK;
@@ -697,17 +1120,46 @@ ry_status ry_poisson_eps_history(ry_poisson* p, double* eps, int32_t cap, int32_
 ry_status ry_poisson_download(ry_poisson* p, int32_t which, double* host) {
   RY_ABI_TRY
   if (!p || !host || which < 0 || which >= RY_PV_COUNT) return RY_EINVAL;
-  Scalars s{};
   PCHK(p, hipStreamSynchronize(p->stream));
-  PCHK(p, hipMemcpy(&s, p->sc, sizeof s, hipMemcpyDeviceToHost));
-  // x r u w z q s p; w_i lives in buffer (i & 1)... after iteration i-1 wrote it
   int slot;
-  switch (which) {
-    case RY_PV_X: slot = 0; break;
-    case RY_PV_R: slot = 1; break;
-    case RY_PV_U: slot = 2; break;
-    case RY_PV_W: slot = 3 + (s.iter & 1); break;
-    default: slot = which + 1; break;   // z q s p -> 5..8
+  if (p->two_sweep) {
+    // x, r and p are kept; the others follow from them, formed in the two
+    // buffers the next iteration overwrites
+    const int cur = int(p->iter & 1), s1 = 1 + (cur ^ 1), s2 = 3 + (cur ^ 1);
+    const int blocks = int(std::min<int64_t>((p->N + 255) / 256, 8192));
+    auto minv = [&](int from, int to) {
+      hipLaunchKernelGGL(minv_kernel, dim3(blocks), dim3(256), 0, p->stream, p->g, p->cfg.precond, p->v[from],
+                         p->v[to]);
+    };
+    auto mul_a = [&](int from, int to) {
+      hipLaunchKernelGGL(apply_a_kernel, dim3(blocks), dim3(256), 0, p->stream, p->g, p->v[from], p->v[to]);
+    };
+    slot = 0;
+    if (which == RY_PV_R) {
+      slot = 1 + cur;
+    } else if (which == RY_PV_P) {
+      slot = 3 + cur;
+    } else if (which == RY_PV_U || which == RY_PV_W) {   // u = M^-1 r, w = A u
+      minv(1 + cur, s1);
+      if (which == RY_PV_W) mul_a(s1, s2);
+      slot = which == RY_PV_W ? s2 : s1;
+    } else if (which != RY_PV_X) {                       // s = A p, q = M^-1 s, z = A q
+      mul_a(3 + cur, s1);
+      if (which != RY_PV_S) minv(s1, s2);
+      if (which == RY_PV_Z) mul_a(s2, s1);
+      slot = which == RY_PV_Q ? s2 : s1;
+    }
+    PCHK(p, hipGetLastError());
+    PCHK(p, hipStreamSynchronize(p->stream));
+  } else {
+    // x r u w z q s p; w_i lives in buffer (i & 1)
+    switch (which) {
+      case RY_PV_X: slot = 0; break;
+      case RY_PV_R: slot = 1; break;
+      case RY_PV_U: slot = 2; break;
+      case RY_PV_W: slot = 3 + int(p->iter & 1); break;
+      default: slot = which + 1; break;   // z q s p -> 5..8
+    }
   }
   PCHK(p, hipMemcpy(host, p->v[slot], sizeof(double) * size_t(p->N), hipMemcpyDeviceToHost));
   return RY_OK;
@@ -720,9 +1172,10 @@ ry_status ry_poisson_scalars(ry_poisson* p, double* alpha_prev, double* gamma_pr
   Scalars s{};
   PCHK(p, hipStreamSynchronize(p->stream));
   PCHK(p, hipMemcpy(&s, p->sc, sizeof s, hipMemcpyDeviceToHost));
-  if (alpha_prev) *alpha_prev = s.alpha_prev;
-  if (gamma_prev) *gamma_prev = s.gamma_prev;
-  if (iter) *iter = s.iter;
+  const Scalars::Step& st = s.step[step_slot(p)];
+  if (alpha_prev) *alpha_prev = st.alpha_prev;
+  if (gamma_prev) *gamma_prev = st.gamma_prev;
+  if (iter) *iter = st.iter;
   return RY_OK;
   RY_ABI_CATCH
 }
