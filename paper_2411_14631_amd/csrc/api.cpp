@@ -80,12 +80,9 @@ struct ry_ctx {
   double* d_lam = nullptr;                // 1 / per box
   double* d_t = nullptr;                  // 1 / per box
   int32_t* d_flags = nullptr;             // [0]=skip [1]=done [2]=nstep [3]=err
-  // pinned host copy of the flags and the time read back after ry_advance
-  // (one round trip for both), allocated on first use
-  struct Readback {
-    int32_t flags[4];
-    double t;
-  };
+  // the flags, the time, the levels' maximum signal speeds and the totals as
+  // the stream's last work left them: written into pinned host memory by one
+  // small kernel ahead of a synchronisation
   Readback* h_rb = nullptr;
   unsigned long long* d_floors = nullptr;
   unsigned int* d_queue = nullptr;        // 8 counters, QUEUE_STRIDE apart
@@ -264,7 +261,17 @@ ry_status init_common(ry_ctx* c) {
   return RY_OK;
 }
 
+// The pinned readback buffer (kept for the context's life).
+ry_status ensure_readback(ry_ctx* c) {
+  if (!c->h_rb && hipHostMalloc(reinterpret_cast<void**>(&c->h_rb), sizeof(Readback)) != hipSuccess) {
+    c->h_rb = nullptr;
+    return fail(c, RY_ENOMEM, "pinned readback buffer");
+  }
+  return RY_OK;
+}
+
 ry_status alloc_scalars(ry_ctx* c, int nslot) {
+  if (ry_status s = ensure_readback(c)) return s;
   c->d_smax = static_cast<double*>(dalloc(c, sizeof(double) * nslot));
   c->d_slots = static_cast<unsigned long long*>(dalloc(c, sizeof(unsigned long long) * nslot * SMAX_SLOTS));
   const int64_t npart = std::max<int64_t>(c->seg_off.back(), 1);
@@ -642,11 +649,14 @@ ry_status enqueue_coarse_step(ry_ctx* c, double t_end) {
   return enqueue_level(c, c->cfg.level_min, 0, true);
 }
 
+// Waits for the stream; *h_rb then holds the device's scalars, and an error
+// latched on the device is reported.
 ry_status sync_and_check(ry_ctx* c) {
+  if (launch_readback(c->d_flags, c->d_t, c->d_smax, c->batch ? 0 : c->nlev, c->d_tot, c->h_rb, c->stream))
+    return fail(c, RY_EHIP, "readback kernel");
   HIPCHK(c, hipStreamSynchronize(c->stream));
   if (c->timing) time_collect(c);
-  int32_t e = 0;
-  HIPCHK(c, hipMemcpy(&e, err_ptr(c), sizeof e, hipMemcpyDeviceToHost));
+  const int32_t e = c->h_rb->flags[3];
   if (e & ERR_BOUNDS) return fail(c, RY_EHIP, "device index outside its buffer (debug build bounds check)");
   if (e) return fail(c, RY_ENUMERIC, "non-finite or non-positive density/energy latched on the device");
   return RY_OK;
@@ -1402,8 +1412,7 @@ ry_status ry_cfl_dt(ry_ctx* c, double* dt) {
   ry_status s = enqueue_cfl_all(c);
   if (s) return s;
   if ((s = sync_and_check(c))) return s;
-  std::vector<double> sm(c->nlev);
-  HIPCHK(c, hipMemcpy(sm.data(), c->d_smax, sizeof(double) * c->nlev, hipMemcpyDeviceToHost));
+  const double* sm = c->h_rb->smax;
   double best = INFINITY;
   for (int k = 0; k < c->nlev; ++k) {
     const double smax = sm[k];
@@ -1494,16 +1503,7 @@ ry_status ry_advance(ry_ctx* c, int32_t n_coarse, double t_end, double* t_io) {
     if (c->count[k] != 0) return fail(c, RY_ESTATE, "ry_advance called inside a coarse step");
   ry_status s;
   if (!c->slots_valid && (s = enqueue_cfl_all(c))) return s;
-  // the time goes up and comes back through a pinned buffer (asynchronous
-  // copies; the ones from pageable memory are staged)
-  if (!c->h_rb && hipHostMalloc(reinterpret_cast<void**>(&c->h_rb), sizeof(ry_ctx::Readback)) != hipSuccess) {
-    c->h_rb = nullptr;
-    return fail(c, RY_ENOMEM, "pinned readback buffer");
-  }
-  c->h_rb->t = *t_io;
-  HIPCHK(c, hipMemcpyAsync(c->d_t, &c->h_rb->t, sizeof(double), hipMemcpyHostToDevice, c->stream));
-  if (launch_zero_u32(reinterpret_cast<unsigned int*>(c->d_flags), 3, c->stream))
-    return fail(c, RY_EHIP, "zero kernel");
+  if (launch_begin(*t_io, c->d_t, c->d_flags, c->stream)) return fail(c, RY_EHIP, "begin kernel");
   const bool use_graph = !c->timing;
   // Buffer parity of the base level before the steps: each executed coarse
   // step flips it once (finer levels take two substeps per coarse step, so
@@ -1529,14 +1529,7 @@ ry_status ry_advance(ry_ctx* c, int32_t n_coarse, double t_end, double* t_io) {
     }
   }
   c->slots_valid = true;
-  // one round trip for the error word, the device's step count and the time
-  HIPCHK(c, hipMemcpyAsync(c->h_rb->flags, c->d_flags, sizeof c->h_rb->flags, hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipMemcpyAsync(&c->h_rb->t, c->d_t, sizeof(double), hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  if (c->timing) time_collect(c);
-  const int32_t e = c->h_rb->flags[3];
-  if (e & ERR_BOUNDS) return fail(c, RY_EHIP, "device index outside its buffer (debug build bounds check)");
-  if (e) return fail(c, RY_ENUMERIC, "non-finite or non-positive density/energy latched on the device");
+  if ((s = sync_and_check(c))) return s;
   const int32_t nrun = c->h_rb->flags[2];
   if (nrun < 0 || nrun > n_coarse) return fail(c, RY_EHIP, "device step count %d out of range", nrun);
   c->lev[0].cur = cur0 ^ (nrun & 1);
@@ -1562,7 +1555,7 @@ ry_status ry_conserved_totals(ry_ctx* c, double* tot) {
   if (launch_totals_final(c->d_partial, nb, nv, c->d_tot, c->stream)) return fail(c, RY_EHIP, "totals kernel");
   ry_status s = sync_and_check(c);
   if (s) return s;
-  HIPCHK(c, hipMemcpy(tot, c->d_tot, sizeof(double) * nv, hipMemcpyDeviceToHost));
+  std::copy(c->h_rb->tot, c->h_rb->tot + nv, tot);
   return RY_OK;
   RY_ABI_CATCH
 }

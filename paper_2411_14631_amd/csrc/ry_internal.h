@@ -258,6 +258,18 @@ struct FinalizeArgs {
   int32_t batch;
 };
 int launch_finalize(const FinalizeArgs& a, void* stream);
+// What a synchronising call reads back: written into pinned host memory by
+// one kernel at the end of the stream's work.
+struct Readback {
+  int32_t flags[4];
+  double t;
+  double smax[RY_MAX_LEVELS];
+  double tot[NVMAX];
+};
+int launch_readback(const int32_t* flags, const double* t, const double* smax, int nsmax, const double* tot,
+                    Readback* host, void* stream);
+// Start of a run of coarse steps: the time, and flags 0-2 (skip, done, steps) cleared.
+int launch_begin(double t, double* d_t, int32_t* flags, void* stream);
 int launch_zero_u32(unsigned int* p, int64_t n, void* stream);
 int launch_zero_u64(unsigned long long* p, int64_t n, void* stream);
 int launch_totals(const double* U, int64_t plane, int64_t n_oct, const uint8_t* refined, double vol, int nv,
