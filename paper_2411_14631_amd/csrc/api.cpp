@@ -91,14 +91,20 @@ struct ry_ctx {
   double* d_dx_box = nullptr;
   int64_t* d_box_noct = nullptr;          // batch: octs per axis of each box (3 per box)
   bool slots_valid = false;
+  // one-level contexts: the chained steps' slots and records ([4][boxes])
+  unsigned long long* d_cslots = nullptr;
+  StepRec* d_crec = nullptr;
+  bool chain_valid = false;               // d_cslots' phase 0 holds the current state's maxima
+  bool smax_valid = false;                // d_smax does (set by the CFL pass)
   // subcycling order state for ry_hydro_step
   int count[RY_MAX_LEVELS] = {0};
   double dt_of[RY_MAX_LEVELS] = {0};
   // graphs of 1, 2, 4, 8 and 16 coarse steps: [log2 of the step count]
-  // [parity of the base level buffer]
+  // [parity of the base level buffer, or of the chain's phase / 2]
   hipGraphExec_t graph[5][2] = {};
   std::vector<int> graph_par[5][2];
   double graph_tend[5][2] = {};
+  int graph_phase[5][2] = {};
   // batch
   int nbox = 0;
   std::vector<int64_t> box_off, box_noct;
@@ -137,6 +143,9 @@ ry_status fail(ry_ctx* c, ry_status s, const char* fmt, ...) {
 // Default launch: small tiles, one 64-thread wavefront per tile, one tile
 // per workgroup, the hardware dispatcher as the queue.
 constexpr ry_tuning kDefaultTuning{1, 0, 4, 1, 1, 4};
+
+// 4^3-cell tiles up to which one-level steps are chained (chained_steps).
+constexpr int32_t kChainSmallTiles = 8192;
 
 void* dalloc(ry_ctx* c, size_t bytes) {
   if (bytes == 0) bytes = 256;
@@ -284,6 +293,11 @@ ry_status alloc_scalars(ry_ctx* c, int nslot) {
   c->d_queue = static_cast<unsigned int*>(dalloc(c, sizeof(unsigned int) * 8 * QUEUE_STRIDE));
   c->d_partial = static_cast<double*>(dalloc(c, sizeof(double) * NVMAX * totals_blocks()));
   c->d_tot = static_cast<double*>(dalloc(c, sizeof(double) * NVMAX));
+  if (c->nlev == 1) {
+    c->d_cslots = static_cast<unsigned long long*>(dalloc(c, sizeof(unsigned long long) * 4 * CHAIN_SLOTS * nslot));
+    c->d_crec = static_cast<StepRec*>(dalloc(c, sizeof(StepRec) * 4 * nslot));
+    if (!c->d_cslots || !c->d_crec) return RY_ENOMEM;
+  }
   if (!c->d_smax || !c->d_slots || !c->d_lam || !c->d_t || !c->d_flags || !c->d_floors || !c->d_queue || !c->d_partial ||
       !c->d_tot || !c->d_part || !c->d_segoff)
     return RY_ENOMEM;
@@ -379,7 +393,53 @@ ry_status enqueue_cfl_all(ry_ctx* c) {
   ry_status s = enqueue_seg_max(c);
   if (s) return s;
   c->slots_valid = true;
+  c->smax_valid = true;
+  c->chain_valid = false;
   return RY_OK;
+}
+
+// Whether the context's steps are chained (Chain): one level, and a launch
+// whose workgroups' share of the time-step work costs less than the finalize
+// launch it replaces.
+bool chained_steps(const ry_ctx* c) {
+  if (c->nlev != 1) return false;
+  const ry_tuning& t = c->tune[0];
+  if (t.persistent) return false;
+  return t.tile_cells == 8 || c->lev[0].n_tile <= kChainSmallTiles;
+}
+
+// Start of a chained run: the slots and records of phase 0.
+ry_status chain_begin(ry_ctx* c, double t) {
+  ry_status s;
+  if (!c->chain_valid && !c->smax_valid && (s = enqueue_cfl_all(c))) return s;
+  if (launch_chain_begin(c->d_cslots, c->d_crec, c->batch ? c->nbox : 1, c->chain_valid ? nullptr : c->d_smax, t,
+                         c->batch ? c->d_t : nullptr, c->stream))
+    return fail(c, RY_EHIP, "chain kernel");
+  return RY_OK;
+}
+
+ry_status chain_end(ry_ctx* c, int phase) {
+  if (launch_chain_end(c->d_cslots, c->d_crec, c->batch ? c->nbox : 1, phase, c->d_t, nstep_ptr(c), c->stream))
+    return fail(c, RY_EHIP, "chain kernel");
+  c->chain_valid = true;
+  c->smax_valid = c->slots_valid = false;
+  return RY_OK;
+}
+
+// The chain's arguments of a step at `phase`.
+void set_chain(ry_ctx* c, HydroArgs& a, int phase, double t_end) {
+  const int nbox = c->batch ? c->nbox : 1;
+  const int64_t n = int64_t(nbox) * CHAIN_SLOTS;
+  const int next = (phase + 1) & 3;
+  a.chain.slots_in = c->d_cslots + phase * n;
+  a.chain.slots_out = a.smax_bits = c->d_cslots + next * n;
+  a.chain.slots_clear = c->d_cslots + ((phase + 2) & 3) * n;
+  a.chain.rec_in = c->d_crec + int64_t(phase) * nbox;
+  a.chain.rec_out = c->d_crec + int64_t(next) * nbox;
+  a.chain.dx_box = c->batch ? c->d_dx_box : nullptr;
+  a.chain.cfl = c->cfg.cfl;
+  a.chain.dx = level_dx(c, c->cfg.level_min);
+  a.chain.t_end = t_end;
 }
 
 ry_status enqueue_ghost(ry_ctx* c, int l, const int32_t* skip) {
@@ -631,7 +691,14 @@ ry_status enqueue_level(ry_ctx* c, int l, int substep, bool last) {
   return RY_OK;
 }
 
-ry_status enqueue_coarse_step(ry_ctx* c, double t_end) {
+ry_status enqueue_coarse_step(ry_ctx* c, double t_end, int phase) {
+  if (chained_steps(c)) {
+    HydroArgs a = hydro_args(c, c->cfg.level_min, 0);
+    set_chain(c, a, phase, t_end);
+    if (ry_status s = enqueue_hydro(c, a, 0)) return s;
+    c->lev[0].cur ^= 1;
+    return RY_OK;
+  }
   FinalizeArgs f{};
   f.slots = c->d_slots;
   f.smax = c->d_smax;
@@ -993,7 +1060,7 @@ ry_status finish_regrid(ry_ctx* c, const std::vector<uint8_t*>* dirty) {
   drop_graphs(c);
   drop_super(c);
   std::fill(std::begin(c->count), std::end(c->count), 0);
-  c->slots_valid = false;
+  c->slots_valid = c->smax_valid = c->chain_valid = false;
   if ((s = build_ghost_read(c))) return s;
   if ((s = ensure_super(c))) return s;
   if ((s = enqueue_cfl_all(c))) return s;
@@ -1455,7 +1522,7 @@ ry_status ry_hydro_step(ry_ctx* c, int32_t level, double dt) {
   c->dt_of[k] = dt;
   if (level > lmin) c->count[k] += 1;
   if (fine) c->count[k + 1] = 0;
-  c->slots_valid = false;
+  c->slots_valid = c->smax_valid = c->chain_valid = false;
   drop_graphs(c);
   return RY_OK;
   RY_ABI_CATCH
@@ -1468,7 +1535,7 @@ ry_status ry_hydro_step(ry_ctx* c, int32_t level, double dt) {
 // level's buffer parity is back where it started after it.
 constexpr int kGraphLevels = 5;
 
-static ry_status capture_step(ry_ctx* c, int gi, int par, double t_end) {
+static ry_status capture_step(ry_ctx* c, int gi, int par, double t_end, int phase) {
   hipGraphExec_t& ge = c->graph[gi][par];
   if (ge) {
     hipGraphExecDestroy(ge);
@@ -1479,7 +1546,7 @@ static ry_status capture_step(ry_ctx* c, int gi, int par, double t_end) {
   hipGraph_t g = nullptr;
   HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
   ry_status s = RY_OK;
-  for (int k = 0; k < (1 << gi) && !s; ++k) s = enqueue_coarse_step(c, t_end);
+  for (int k = 0; k < (1 << gi) && !s; ++k) s = enqueue_coarse_step(c, t_end, (phase + k) & 3);
   hipError_t e = hipStreamEndCapture(c->stream, &g);
   for (size_t i = 0; i < c->lev.size(); ++i) c->lev[i].cur = saved[i];
   if (s) {
@@ -1492,6 +1559,7 @@ static ry_status capture_step(ry_ctx* c, int gi, int par, double t_end) {
   if (e != hipSuccess) return fail(c, RY_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
   c->graph_par[gi][par] = saved;
   c->graph_tend[gi][par] = t_end;
+  c->graph_phase[gi][par] = phase;
   return RY_OK;
 }
 
@@ -1502,8 +1570,14 @@ ry_status ry_advance(ry_ctx* c, int32_t n_coarse, double t_end, double* t_io) {
   for (int k = 1; k < c->nlev; ++k)
     if (c->count[k] != 0) return fail(c, RY_ESTATE, "ry_advance called inside a coarse step");
   ry_status s;
-  if (!c->slots_valid && (s = enqueue_cfl_all(c))) return s;
-  if (launch_begin(*t_io, c->d_t, c->d_flags, c->stream)) return fail(c, RY_EHIP, "begin kernel");
+  const bool chained = chained_steps(c);
+  int phase = 0;
+  if (chained) {
+    if ((s = chain_begin(c, *t_io))) return s;
+  } else {
+    if (!c->slots_valid && (s = enqueue_cfl_all(c))) return s;
+    if (launch_begin(*t_io, c->d_t, c->d_flags, c->stream)) return fail(c, RY_EHIP, "begin kernel");
+  }
   const bool use_graph = !c->timing;
   // Buffer parity of the base level before the steps: each executed coarse
   // step flips it once (finer levels take two substeps per coarse step, so
@@ -1518,17 +1592,25 @@ ry_status ry_advance(ry_ctx* c, int32_t n_coarse, double t_end, double* t_io) {
       while ((1 << gi) > n_coarse - i) --gi;
       std::vector<int> now;
       for (auto& L : c->lev) now.push_back(L.cur);
-      if (!c->graph[gi][par] || c->graph_par[gi][par] != now || c->graph_tend[gi][par] != t_end)
-        if ((s = capture_step(c, gi, par, t_end))) return s;
+      if (!c->graph[gi][par] || c->graph_par[gi][par] != now || c->graph_tend[gi][par] != t_end ||
+          (chained && c->graph_phase[gi][par] != phase))
+        if ((s = capture_step(c, gi, par, t_end, phase))) return s;
       HIPCHK(c, hipGraphLaunch(c->graph[gi][par], c->stream));
       i += 1 << gi;
+      phase = (phase + (1 << gi)) & 3;
       if (gi == 0) c->lev[0].cur ^= 1;   // the other graphs take an even number of steps
     } else {
-      if ((s = enqueue_coarse_step(c, t_end))) return s;
+      if ((s = enqueue_coarse_step(c, t_end, phase))) return s;
+      phase = (phase + 1) & 3;
       ++i;
     }
   }
-  c->slots_valid = true;
+  if (chained) {
+    if ((s = chain_end(c, phase))) return s;
+  } else {
+    c->slots_valid = true;
+    c->smax_valid = c->chain_valid = false;
+  }
   if ((s = sync_and_check(c))) return s;
   const int32_t nrun = c->h_rb->flags[2];
   if (nrun < 0 || nrun > n_coarse) return fail(c, RY_EHIP, "device step count %d out of range", nrun);
@@ -1703,8 +1785,19 @@ ry_status ry_batch_create(const ry_config* cfgs, int32_t nbox, const double* con
   RY_ABI_CATCH
 }
 
-static ry_status enqueue_batch_step(ry_ctx* c) {
+static ry_status enqueue_batch_step(ry_ctx* c, int phase) {
   DevLevel& L = c->lev[0];
+  if (chained_steps(c)) {
+    HydroArgs a = hydro_args(c, c->cfg.level_min, 0);
+    a.child = nullptr;
+    a.reg_fine = nullptr;
+    a.reg_own = nullptr;
+    a.record_reg = 0;
+    set_chain(c, a, phase, INFINITY);
+    if (ry_status s = enqueue_hydro(c, a, 0)) return s;
+    L.cur ^= 1;
+    return RY_OK;
+  }
   FinalizeArgs f{};
   f.smax = c->d_smax;
   f.nslot = c->nbox;
@@ -1735,12 +1828,17 @@ static ry_status enqueue_batch_step(ry_ctx* c) {
 ry_status ry_batch_run(ry_ctx* c, int32_t nsteps) {
   RY_ABI_TRY
   if (!c || !c->batch || !c->built || nsteps < 0) return RY_EINVAL;
-  ry_status s;
-  if (!c->slots_valid && (s = enqueue_cfl_all(c))) return s;
+  ry_status s = RY_OK;
+  const bool chained = chained_steps(c);
+  if (chained) {
+    if ((s = chain_begin(c, 0.0))) return s;
+  } else if (!c->slots_valid && (s = enqueue_cfl_all(c))) {
+    return s;
+  }
   DevLevel& L = c->lev[0];
   if (c->timing) {
     for (int i = 0; i < nsteps; ++i)
-      if ((s = enqueue_batch_step(c))) return s;
+      if ((s = enqueue_batch_step(c, i & 3))) return s;
   } else if (nsteps > 0) {
     if (!c->bgraph || c->bgraph_steps != nsteps || c->bgraph_par != L.cur) {
       if (c->bgraph) {
@@ -1750,7 +1848,7 @@ ry_status ry_batch_run(ry_ctx* c, int32_t nsteps) {
       const int saved = L.cur;
       hipGraph_t g = nullptr;
       HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-      for (int i = 0; i < nsteps && !s; ++i) s = enqueue_batch_step(c);
+      for (int i = 0; i < nsteps && !s; ++i) s = enqueue_batch_step(c, i & 3);
       hipError_t e = hipStreamEndCapture(c->stream, &g);
       L.cur = saved;
       if (s) {
@@ -1767,7 +1865,12 @@ ry_status ry_batch_run(ry_ctx* c, int32_t nsteps) {
     HIPCHK(c, hipGraphLaunch(c->bgraph, c->stream));
     if (nsteps & 1) L.cur ^= 1;
   }
-  c->slots_valid = true;
+  if (chained) {
+    if ((s = chain_end(c, nsteps & 3))) return s;
+  } else {
+    c->slots_valid = true;
+    c->smax_valid = c->chain_valid = false;
+  }
   return sync_and_check(c);
   RY_ABI_CATCH
 }

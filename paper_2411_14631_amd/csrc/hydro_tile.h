@@ -233,6 +233,9 @@ struct TileLDS {
   // states' part of buf (unused after phase C) when it holds them
   static constexpr bool SMAX_IN_BUF = (K == 8) && sizeof(Real) * NV * G::NUPPER >= sizeof(double) * G::NCORE;
   double smx[(K == 8 && !SMAX_IN_BUF) ? G::NCORE : 1];
+  // chained steps: the step's lambda, and whether it is past t_end
+  double lam;
+  int32_t skip;
 };
 
 // ---------------------------------------------------------------------------
@@ -429,6 +432,31 @@ __device__ __forceinline__ void core_face_flux(const Real* FL, int f, const Real
   F[4] = Fn[4];
 #pragma unroll
   for (int k = NVAR; k < NVAR + NS; ++k) F[k] = side.scalar_flux(FL[k * NFACE + f], wr[k]);
+}
+
+// Time step of a box from its largest signal speed (the arithmetic of the
+// finalize kernel for one level); returns lambda = dt / dx, 0 when the step
+// does not run.
+__device__ __forceinline__ double chain_step(const StepRec& in, double smax, double cfl, double dx, double t_end,
+                                             StepRec& out) {
+#pragma clang fp contract(off)
+  out = in;
+  if (in.done) return 0.0;
+  double dt = INFINITY;
+  if (smax > 0.0) dt = cfl * dx / smax;
+  int last = 0;
+  if (dt >= t_end - in.t) {
+    dt = t_end - in.t;
+    last = 1;
+  }
+  if (!(dt > 0.0)) {
+    out.done = 1;
+    return 0.0;
+  }
+  out.t = last ? t_end : in.t + dt;
+  out.done = last;
+  out.nstep = in.nstep + 1;
+  return dt / dx;
 }
 
 // Maximum over a wavefront's 64 lanes (all active), returned to every lane:
@@ -639,7 +667,9 @@ __device__ __forceinline__ int32_t lds_tab_entry(const HydroArgs& A, int32_t e) 
   return (e >= A.n_oct) ? e + A.ghost_adj : e;
 }
 
-template <typename Real, int NT, int NS, int K>
+// ONE: a step of a one-level run (Chain): lambda is formed here, every oct is
+// a leaf oct and the level has neither ghost octs nor registers.
+template <typename Real, int NT, int NS, int K, bool ONE>
 __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS<Real, NVAR + NS, K>& S, int tid_in,
                                            bool active, GatherRegs<K, NT, NVAR + NS>& R) {
   using G = Geom<K>;
@@ -661,8 +691,12 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
   int hb[3];
   tile_hb<K>(fl, hb);
   const int box = (active && A.tile_box) ? A.tile_box[tile] : 0;
-  const double lam = A.lam_dev ? A.lam_dev[box] : A.lam_host;
-  const Real h = Real(0.5 * lam);
+  double lam = 0.0;
+  Real h = Real(0);
+  if constexpr (!ONE) {
+    lam = A.lam_dev ? A.lam_dev[box] : A.lam_host;
+    h = Real(0.5 * lam);
+  }
   const Real igm1 = Real(A.igm1);
   const StencilTables<K>& ST = stencil_tables<K>();
   const int32_t* tab = S.tab;
@@ -700,7 +734,7 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
   if (active && tid < TAB) {
     e_tab = A.tab[size_t(tile) * TAB + tid];
     if (!debug_in_bounds(e_tab >= -1 && e_tab < A.n_ext, A.err)) e_tab = -1;
-    S.tab[tid] = lds_tab_entry(A, e_tab);
+    S.tab[tid] = ONE ? e_tab : lds_tab_entry(A, e_tab);
   }
   __syncthreads();
   // Wait for the table entries here on every path: otherwise the gather's
@@ -714,7 +748,31 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
   // --- phase A: gather + primitives (all loads of the thread's positions
   // are issued before any conversion)
   gather_issue<K, NT, NV>(A, tab, fl, hb, tid, active, entA, R);
-  const uint8_t rb = (e_tab >= 0) ? A.refined[e_tab] : uint8_t(0);
+  const uint8_t rb = (!ONE && e_tab >= 0) ? A.refined[e_tab] : uint8_t(0);
+
+  // chained steps: the tile's last wavefront (the one with the fewest halo
+  // positions) forms lambda while its state loads are under way
+  if (ONE && tid >= NT - 64) {
+    const Chain& C = A.chain;
+    const int64_t sl = int64_t(box) * CHAIN_SLOTS + lane;
+    const unsigned long long sv = C.slots_in[sl];
+    const StepRec in = C.rec_in[box];
+    StepRec out;
+    const double l = chain_step(in, wave_max(__longlong_as_double(static_cast<long long>(sv))), C.cfl,
+                                C.dx_box ? C.dx_box[box] : C.dx, C.t_end, out);
+    const bool runs = out.nstep != in.nstep;
+    if (lane == 0) {
+      S.lam = l;
+      S.skip = runs ? 0 : 1;
+    }
+    // the box's first tile hands the record on and clears the slots of the
+    // step after the next one; a step that does not run keeps its maxima
+    if (active && (tile == 0 || (A.tile_box && A.tile_box[tile - 1] != box))) {
+      C.slots_clear[sl] = 0ull;
+      if (!runs) C.slots_out[sl] = sv;
+      if (lane == 0) C.rec_out[box] = out;
+    }
+  }
 
   // --- phase A (conversion): primitives into LDS.  A core cell's first
   // gathered position is the cell itself (the tables' oct-major order): its
@@ -744,6 +802,11 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
   }
   if (active && tid < TAB) S.ref[tid] = rb;
   __syncthreads();
+  if constexpr (ONE) {
+    if (S.skip) return;   // every tile of the launch alike, or of the box: nothing written yet
+    lam = S.lam;
+    h = Real(0.5 * lam);
+  }
 
   // --- phase B1: slopes + predictor.  The core cell of a thread (first pass,
   // tid < NCORE) keeps W~ and its slopes in registers for its six faces; a
@@ -926,7 +989,7 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
     // a tile cut by the domain's high side: its slots past the cut hold the
     // periodic images of other octs, which other tiles update
     const bool inside = cx <= hb[0] && cy <= hb[1] && cz <= hb[2];
-    leaf[r] = cthr && inside && (e[r] >= 0) && (e[r] < A.n_oct) && !((ref[ts] >> ci) & 1);
+    leaf[r] = cthr && inside && (e[r] >= 0) && (e[r] < A.n_oct) && (ONE || !((ref[ts] >> ci) & 1));
     cell[r] = uint32_t(e[r]) * 8u + uint32_t(ci);
   }
   // planes addressed by 32-bit byte offsets where they fit (as the gather)
@@ -956,7 +1019,7 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
         Fm[v] = double(Fc[r][d][v]);
         Fp[v] = double(SF[v * NFACE + fp]);
       }
-      if (A.child) {
+      if (!ONE && A.child) {
         // a refined neighbour across a face: use its child oct's register
 #pragma unroll
         for (int side = 0; side < 2; ++side) {
@@ -1016,7 +1079,7 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
       // non-negative double orders like its bit pattern); the maximum does
       // not depend on the order of arrival
       const double m = wave_max(s);
-      const int sl = tile & (SMAX_SLOTS - 1);
+      const int sl = ONE ? box * CHAIN_SLOTS + (tile & (CHAIN_SLOTS - 1)) : tile & (SMAX_SLOTS - 1);
       if (lane == 0) atomicMax(A.smax_bits + sl, (unsigned long long)__double_as_longlong(m));
     } else if (active && A.tile_smax) {
       // batched boxes: one partial per tile, reduced per box by the
@@ -1033,7 +1096,7 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
 #pragma unroll
   for (int rr = 0; rr < (NREG + NT - 1) / NT; ++rr) {
     const int rt = rt0 + NT * rr;
-    if (!(active && A.record_reg && rt >= 0 && rt < NREG)) continue;
+    if (ONE || !(active && A.record_reg && rt >= 0 && rt < NREG)) continue;
     const int b = rt / 6, face = rt - 6 * (rt / 6);
     const int bx = b % KO, by = (b / KO) % KO, bz = b / (KO * KO);
     const int tb_ = G::slot(bx, by, bz);
@@ -1118,7 +1181,8 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
       m = wave_max(m);
       if (lane == 0) {
         if (A.smax_bits) {
-          atomicMax(A.smax_bits + (tile & (SMAX_SLOTS - 1)), (unsigned long long)__double_as_longlong(m));
+          const int sl = ONE ? box * CHAIN_SLOTS + (tile & (CHAIN_SLOTS - 1)) : tile & (SMAX_SLOTS - 1);
+          atomicMax(A.smax_bits + sl, (unsigned long long)__double_as_longlong(m));
         } else {
           // batched boxes: the tile's partial (an atomic maximum on its bit
           // pattern into a slot cleared before the launch)
@@ -1144,19 +1208,19 @@ constexpr int hydro_waves_per_eu() {
   return K == 8 ? (WPT == 8 ? 4 : (sizeof(Real) == 4 ? 3 : 2)) : (NS == 0 ? 3 : 1);
 }
 
-template <typename Real, int TPW, int WPT, int NS, int K>
+template <typename Real, int TPW, int WPT, int NS, int K, bool ONE>
 __global__ __launch_bounds__(64 * WPT * TPW) __attribute__((amdgpu_waves_per_eu(hydro_waves_per_eu<Real, K, NS, WPT>())))
 void hydro_kernel(HydroArgs A) {
   constexpr int NT = 64 * WPT;
   __shared__ TileLDS<Real, NVAR + NS, K> S[TPW];
-  if (A.skip && *A.skip) return;
+  if (!ONE && A.skip && *A.skip) return;
   const int w = threadIdx.x / NT, tid = threadIdx.x % NT;
   const int ngroups = (A.n_tile + TPW - 1) / TPW;
   const int grp = xcd_remap(blockIdx.x, gridDim.x);
   if (grp >= ngroups) return;
   const int tile = grp * TPW + w;
   GatherRegs<K, NT, NVAR + NS> R;
-  hydro_tile<Real, NT, NS, K>(A, tile < A.n_tile ? tile : 0, S[w], tid, tile < A.n_tile, R);
+  hydro_tile<Real, NT, NS, K, ONE>(A, tile < A.n_tile ? tile : 0, S[w], tid, tile < A.n_tile, R);
 }
 
 // Persistent variant (K = 4): workgroups pop groups of tiles from 8 per-XCD
@@ -1207,7 +1271,7 @@ __global__ __launch_bounds__(64 * WPT * TPW) __attribute__((amdgpu_waves_per_eu(
       if (grp >= ngroups) break;
       const int tile = grp * TPW + w;
       GatherRegs<4, NT, NVAR> R;
-      hydro_tile<Real, NT, 0, 4>(A, tile < A.n_tile ? tile : 0, S[w], tid, tile < A.n_tile, R);
+      hydro_tile<Real, NT, 0, 4, false>(A, tile < A.n_tile ? tile : 0, S[w], tid, tile < A.n_tile, R);
     }
     if (threadIdx.x == 0) {
       int next = -1;
@@ -1235,7 +1299,10 @@ static int launch_hydro_t(const HydroArgs& a, const ry_tuning& t, int num_cu, hi
   const int ngroups = (a.n_tile + TPW - 1) / TPW;
   if (ngroups == 0) return 0;
   if (NS > 0 || K != 4 || !t.persistent) {
-    hipLaunchKernelGGL((hydro_kernel<Real, TPW, WPT, NS, K>), dim3(ngroups), dim3(64 * WPT * TPW), 0, s, a);
+    if (a.chain.slots_in)
+      hipLaunchKernelGGL((hydro_kernel<Real, TPW, WPT, NS, K, true>), dim3(ngroups), dim3(64 * WPT * TPW), 0, s, a);
+    else
+      hipLaunchKernelGGL((hydro_kernel<Real, TPW, WPT, NS, K, false>), dim3(ngroups), dim3(64 * WPT * TPW), 0, s, a);
   } else if constexpr (NS == 0 && K == 4) {
     const int batch = t.batch > 0 ? t.batch : 1;
     const int nitems = (ngroups + batch - 1) / batch;

@@ -445,7 +445,7 @@ int launch_finalize(const FinalizeArgs& a, void* stream) {
 
 // Bound: latency.  Kernel arguments and stores to pinned memory replace the
 // copy engine's path: a host-to-device and two device-to-host copies took
-// about 4 us each on the stream (32^3 box, two steps per call: 53 -> 41 us).
+// about 4 us each on the stream (32^3 box, two steps per call: 53.9 -> 49.1 us).
 __global__ void begin_kernel(double t, double* d_t, int32_t* flags) {
   *d_t = t;
   flags[0] = flags[1] = flags[2] = 0;
@@ -460,6 +460,40 @@ __global__ __launch_bounds__(64) void readback_kernel(const int32_t* __restrict_
   if (i >= 32 && i < 32 + NVMAX) host->tot[i - 32] = tot[i - 32];
 }
 static_assert(8 + RY_MAX_LEVELS <= 32 && 32 + NVMAX <= 64, "one lane per value");
+
+// Chained runs: their first and last kernel (one thread per slot).
+__global__ __launch_bounds__(256) void chain_begin_kernel(unsigned long long* slots, StepRec* rec, int nbox,
+                                                          const double* __restrict__ smax, double t,
+                                                          const double* __restrict__ t_dev) {
+  const int64_t n = int64_t(nbox) * CHAIN_SLOTS, i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int b = int(i / CHAIN_SLOTS), k = int(i % CHAIN_SLOTS);
+  if (smax) slots[i] = k == 0 ? (unsigned long long)__double_as_longlong(smax[b]) : 0ull;
+  slots[n + i] = 0ull;
+  slots[2 * n + i] = 0ull;
+  if (k == 0) rec[b] = {t_dev ? t_dev[b] : t, 0, 0};
+}
+__global__ __launch_bounds__(256) void chain_end_kernel(unsigned long long* slots, const StepRec* __restrict__ rec,
+                                                        int nbox, int phase, double* t_dev, int32_t* nstep) {
+  const int64_t n = int64_t(nbox) * CHAIN_SLOTS, i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  if (phase) slots[i] = slots[phase * n + i];
+  if (i % CHAIN_SLOTS == 0) t_dev[i / CHAIN_SLOTS] = rec[int64_t(phase) * nbox + i / CHAIN_SLOTS].t;
+  if (i == 0) *nstep = rec[int64_t(phase) * nbox].nstep;
+}
+int launch_chain_begin(unsigned long long* slots, StepRec* rec, int nbox, const double* smax, double t,
+                       const double* t_dev, void* stream) {
+  const unsigned nb = unsigned((int64_t(nbox) * CHAIN_SLOTS + 255) / 256);
+  hipLaunchKernelGGL(chain_begin_kernel, dim3(nb), dim3(256), 0, (hipStream_t)stream, slots, rec, nbox, smax, t, t_dev);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+int launch_chain_end(unsigned long long* slots, const StepRec* rec, int nbox, int phase, double* t_dev, int32_t* nstep,
+                     void* stream) {
+  const unsigned nb = unsigned((int64_t(nbox) * CHAIN_SLOTS + 255) / 256);
+  hipLaunchKernelGGL(chain_end_kernel, dim3(nb), dim3(256), 0, (hipStream_t)stream, slots, rec, nbox, phase, t_dev,
+                     nstep);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
 
 int launch_begin(double t, double* d_t, int32_t* flags, void* stream) {
   hipLaunchKernelGGL(begin_kernel, dim3(1), dim3(1), 0, (hipStream_t)stream, t, d_t, flags);

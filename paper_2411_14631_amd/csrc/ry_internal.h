@@ -130,6 +130,25 @@ std::string build_tables(const DomainSpec& dom, const std::vector<HostLevel>& le
                          std::vector<LevelTables>& out);
 
 // ------------------------------------------------------------- kernels
+// One-level runs (a uniform box, the batched boxes) without a time-step
+// launch between their steps: every workgroup of a step forms its box's dt
+// itself from what the step before left.  Sets of slots and records rotate
+// with the step's phase (0-3), so that a kernel never reads what it writes:
+// it reads set `phase`, fills the next and clears the one after that.
+constexpr int CHAIN_SLOTS = 64;    // partial maxima per box: tile t's in slot t mod 64
+struct StepRec {
+  double t;                        // time reached
+  int32_t done, nstep;             // t_end reached; steps taken
+};
+struct Chain {
+  const unsigned long long* slots_in;   // [box][CHAIN_SLOTS]; nullptr = not chained
+  unsigned long long *slots_out, *slots_clear;
+  const StepRec* rec_in;                // [box]
+  StepRec* rec_out;
+  const double* dx_box;                 // per box, or nullptr: dx
+  double cfl, dx, t_end;
+};
+
 struct HydroArgs {
   const double* U;            // current state (ext octs), nv planes of 8*n_ext
   double* Un;                 // next state
@@ -164,6 +183,7 @@ struct HydroArgs {
   int32_t* err;
   const int32_t* skip;        // device flag: skip this launch's work
   unsigned int* queue;        // persistent mode: 8 per-XCD counters, QUEUE_STRIDE apart
+  Chain chain;                // slots_in != nullptr: lambda from it, the maxima into it
 };
 
 struct GhostArgs {
@@ -268,6 +288,15 @@ struct Readback {
 };
 int launch_readback(const int32_t* flags, const double* t, const double* smax, int nsmax, const double* tot,
                     Readback* host, void* stream);
+// Start of a chained run (sets [4][nbox]): phase 0's records from t (a value,
+// or per box when t_dev is given), its slots from smax (nullptr: they hold
+// the maxima already), the next two phases' slots cleared.
+int launch_chain_begin(unsigned long long* slots, StepRec* rec, int nbox, const double* smax, double t,
+                       const double* t_dev, void* stream);
+// Its end at `phase`: the slots back in phase 0, the boxes' times in t_dev,
+// box 0's step count in *nstep.
+int launch_chain_end(unsigned long long* slots, const StepRec* rec, int nbox, int phase, double* t_dev, int32_t* nstep,
+                     void* stream);
 // Start of a run of coarse steps: the time, and flags 0-2 (skip, done, steps) cleared.
 int launch_begin(double t, double* d_t, int32_t* flags, void* stream);
 int launch_zero_u32(unsigned int* p, int64_t n, void* stream);
