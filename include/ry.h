@@ -105,8 +105,10 @@ ry_status ry_cfl_dt(ry_ctx* ctx, double* dt_coarse);
 ry_status ry_hydro_step(ry_ctx* ctx, int32_t level, double dt);
 
 /* Up to n_coarse coarse steps, each with dt from the CFL rule clipped to
- * reach t_end exactly; dt stays on the device (no host sync per step);
- * steps are replayed from a captured hipGraph.  *t_io: time in/out.  Syncs. */
+ * reach t_end exactly; dt stays on the device (no host sync per step).  A
+ * step of one level is one launch; steps of several levels are replayed from
+ * captured hipGraphs once a call length comes by a second time on the same
+ * mesh and tuning.  *t_io: time in/out.  Syncs. */
 ry_status ry_advance(ry_ctx* ctx, int32_t n_coarse, double t_end, double* t_io);
 
 /* Regrid between coarse steps (dynamic refinement, the refine_fine step of
@@ -151,8 +153,9 @@ ry_status ry_upload(ry_ctx* ctx, int32_t level, const double* U);
  * if the boxes' octs together reach 2^29. */
 ry_status ry_batch_create(const ry_config* cfgs, int32_t nbox, const double* const* U0, ry_ctx** out);
 /* nsteps steps of every box, each box with its own CFL dt computed on the
- * device, as one captured graph (reused while nsteps and the state parity
- * repeat) of one hydro launch per step over the tiles of all boxes.
+ * device, one hydro launch per step over the tiles of all boxes (with the
+ * queue-fed tuning, and with 4^3-cell tiles past 8192 of them, a captured
+ * graph of the steps, reused while nsteps and the state parity repeat).
  * Syncs. */
 ry_status ry_batch_run(ry_ctx* ctx, int32_t nsteps);
 ry_status ry_batch_box_info(const ry_ctx* ctx, int32_t box, int64_t* n_oct, double* t);

@@ -100,11 +100,11 @@ struct ry_ctx {
   int count[RY_MAX_LEVELS] = {0};
   double dt_of[RY_MAX_LEVELS] = {0};
   // graphs of 1, 2, 4, 8 and 16 coarse steps: [log2 of the step count]
-  // [parity of the base level buffer, or of the chain's phase / 2]
+  // [parity of the base level buffer]
   hipGraphExec_t graph[5][2] = {};
   std::vector<int> graph_par[5][2];
   double graph_tend[5][2] = {};
-  int graph_phase[5][2] = {};
+  bool graph_asked[5][2] = {};            // a run of that length has come by since the graphs were dropped
   // batch
   int nbox = 0;
   std::vector<int64_t> box_off, box_noct;
@@ -763,6 +763,7 @@ ry_status upload_level_state(ry_ctx* c, DevLevel& D, const double* U_host) {
 }
 
 void drop_graphs(ry_ctx* c) {
+  for (auto& a : c->graph_asked) a[0] = a[1] = false;
   for (auto& gs : c->graph)
     for (auto& g : gs)
       if (g) {
@@ -1535,7 +1536,7 @@ ry_status ry_hydro_step(ry_ctx* c, int32_t level, double dt) {
 // level's buffer parity is back where it started after it.
 constexpr int kGraphLevels = 5;
 
-static ry_status capture_step(ry_ctx* c, int gi, int par, double t_end, int phase) {
+static ry_status capture_step(ry_ctx* c, int gi, int par, double t_end) {
   hipGraphExec_t& ge = c->graph[gi][par];
   if (ge) {
     hipGraphExecDestroy(ge);
@@ -1546,7 +1547,7 @@ static ry_status capture_step(ry_ctx* c, int gi, int par, double t_end, int phas
   hipGraph_t g = nullptr;
   HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
   ry_status s = RY_OK;
-  for (int k = 0; k < (1 << gi) && !s; ++k) s = enqueue_coarse_step(c, t_end, (phase + k) & 3);
+  for (int k = 0; k < (1 << gi) && !s; ++k) s = enqueue_coarse_step(c, t_end, 0);
   hipError_t e = hipStreamEndCapture(c->stream, &g);
   for (size_t i = 0; i < c->lev.size(); ++i) c->lev[i].cur = saved[i];
   if (s) {
@@ -1559,7 +1560,6 @@ static ry_status capture_step(ry_ctx* c, int gi, int par, double t_end, int phas
   if (e != hipSuccess) return fail(c, RY_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
   c->graph_par[gi][par] = saved;
   c->graph_tend[gi][par] = t_end;
-  c->graph_phase[gi][par] = phase;
   return RY_OK;
 }
 
@@ -1578,7 +1578,10 @@ ry_status ry_advance(ry_ctx* c, int32_t n_coarse, double t_end, double* t_io) {
     if (!c->slots_valid && (s = enqueue_cfl_all(c))) return s;
     if (launch_begin(*t_io, c->d_t, c->d_flags, c->stream)) return fail(c, RY_EHIP, "begin kernel");
   }
-  const bool use_graph = !c->timing;
+  // a chained step is one launch: enqueued directly it costs the host about
+  // 2.5 us while the step runs, a graph launch 8 us before it does (32^3, two
+  // steps per call: 36.9 against 45 us; 64^3, eight: 224 against 229)
+  const bool use_graph = !c->timing && !chained;
   // Buffer parity of the base level before the steps: each executed coarse
   // step flips it once (finer levels take two substeps per coarse step, so
   // theirs come back).  Steps enqueued after t_end is reached are skipped on
@@ -1592,12 +1595,19 @@ ry_status ry_advance(ry_ctx* c, int32_t n_coarse, double t_end, double* t_io) {
       while ((1 << gi) > n_coarse - i) --gi;
       std::vector<int> now;
       for (auto& L : c->lev) now.push_back(L.cur);
-      if (!c->graph[gi][par] || c->graph_par[gi][par] != now || c->graph_tend[gi][par] != t_end ||
-          (chained && c->graph_phase[gi][par] != phase))
-        if ((s = capture_step(c, gi, par, t_end, phase))) return s;
+      const bool have = c->graph[gi][par] && c->graph_par[gi][par] == now && c->graph_tend[gi][par] == t_end;
+      if (!have && !c->graph_asked[gi][par]) {
+        // the first time on this mesh and tuning: launched one by one, which
+        // costs less than capturing a graph that may never be used again
+        c->graph_asked[gi][par] = true;
+        for (int k = 0; k < (1 << gi); ++k)
+          if ((s = enqueue_coarse_step(c, t_end, 0))) return s;
+        i += 1 << gi;
+        continue;
+      }
+      if (!have && (s = capture_step(c, gi, par, t_end))) return s;
       HIPCHK(c, hipGraphLaunch(c->graph[gi][par], c->stream));
       i += 1 << gi;
-      phase = (phase + (1 << gi)) & 3;
       if (gi == 0) c->lev[0].cur ^= 1;   // the other graphs take an even number of steps
     } else {
       if ((s = enqueue_coarse_step(c, t_end, phase))) return s;
@@ -1836,7 +1846,7 @@ ry_status ry_batch_run(ry_ctx* c, int32_t nsteps) {
     return s;
   }
   DevLevel& L = c->lev[0];
-  if (c->timing) {
+  if (c->timing || chained) {   // chained: one launch per step, no graph (as in ry_advance)
     for (int i = 0; i < nsteps; ++i)
       if ((s = enqueue_batch_step(c, i & 3))) return s;
   } else if (nsteps > 0) {
@@ -1848,7 +1858,7 @@ ry_status ry_batch_run(ry_ctx* c, int32_t nsteps) {
       const int saved = L.cur;
       hipGraph_t g = nullptr;
       HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-      for (int i = 0; i < nsteps && !s; ++i) s = enqueue_batch_step(c, i & 3);
+      for (int i = 0; i < nsteps && !s; ++i) s = enqueue_batch_step(c, 0);
       hipError_t e = hipStreamEndCapture(c->stream, &g);
       L.cur = saved;
       if (s) {
