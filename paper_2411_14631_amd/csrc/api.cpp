@@ -77,6 +77,7 @@ struct ry_ctx {
   double* d_part = nullptr;               // per-tile (or per-block) partial maxima
   int64_t* d_segoff = nullptr;            // tile offsets of levels / boxes in d_part
   std::vector<int64_t> seg_off;           // host copy
+  int64_t part_cap = 0;                   // values d_part holds
   double* d_lam = nullptr;                // 1 / per box
   double* d_t = nullptr;                  // 1 / per box
   int32_t* d_flags = nullptr;             // [0]=skip [1]=done [2]=nstep [3]=err
@@ -285,6 +286,7 @@ ry_status alloc_scalars(ry_ctx* c, int nslot) {
   c->d_slots = static_cast<unsigned long long*>(dalloc(c, sizeof(unsigned long long) * nslot * SMAX_SLOTS));
   const int64_t npart = std::max<int64_t>(c->seg_off.back(), 1);
   c->d_part = static_cast<double*>(dalloc(c, sizeof(double) * npart));
+  c->part_cap = npart;
   c->d_segoff = static_cast<int64_t*>(dalloc(c, sizeof(int64_t) * c->seg_off.size()));
   c->d_lam = static_cast<double*>(dalloc(c, sizeof(double) * nslot));
   c->d_t = static_cast<double*>(dalloc(c, sizeof(double) * nslot));
@@ -549,14 +551,13 @@ ry_status build_super(ry_ctx* c, int k) {
       D.tile_box = L.tile_box;
       D.box_noct = c->d_box_noct;
     }
-    int32_t ns = 0;
     if (launch_super_keys(L.tab, nt, L.doc, L.n_oct, D, skey, ssub, start, c->stream) ||
-        launch_scan(start, excl, nt, stmp, c->stream) ||
-        hipMemcpyAsync(&ns, stmp + ntmp - 1, sizeof ns, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
+        launch_scan(start, excl, nt, stmp, c->h_rb->rg.total, c->stream) ||
         hipStreamSynchronize(c->stream) != hipSuccess) {
       release();
       return fail(c, RY_EHIP, "super-tile key kernels");
     }
+    const int32_t ns = c->h_rb->rg.total[0];
     auto* sub = static_cast<int32_t*>(A(sizeof(int32_t) * 8 * std::max(ns, 1)));
     auto* sblock = static_cast<uint64_t*>(A(sizeof(uint64_t) * std::max(ns, 1)));
     L.stab = static_cast<int32_t*>(dalloc(c, sizeof(int32_t) * super_table_slots() * std::max(ns, 1)));
@@ -624,11 +625,6 @@ ry_status ensure_super(ry_ctx* c) {
     }
   }
   return RY_OK;
-}
-
-// Super-tile tables of every level are stale (the mesh changed).
-void drop_super(ry_ctx* c) {
-  for (auto& L : c->lev) free_super(c, L);
 }
 
 // One hydro launch of level k with the level's tuning (or `t`): on the small
@@ -922,7 +918,7 @@ ry_status refresh_host_topology(ry_ctx* c) {
   return RY_OK;
 }
 
-ry_status finish_regrid(ry_ctx* c, const std::vector<uint8_t*>* dirty = nullptr);
+ry_status finish_regrid(ry_ctx* c, bool device, const std::vector<uint8_t*>* dirty = nullptr);
 
 // Regrid with flags and tables built on the host (the state stays on the
 // device).
@@ -1018,7 +1014,7 @@ ry_status regrid_host(ry_ctx* c, int64_t* n_created, int64_t* n_destroyed) {
     c->built = false;
     return fail(c, RY_ENOMEM, "regrid allocation failed; the context must be rebuilt");
   }
-  if ((s = finish_regrid(c))) return s;
+  if ((s = finish_regrid(c, false))) return s;
   if (n_created) *n_created = created;
   if (n_destroyed) *n_destroyed = destroyed;
   return RY_OK;
@@ -1029,19 +1025,21 @@ ry_status regrid_host(ry_ctx* c, int64_t* n_created, int64_t* n_destroyed) {
 // dirty (device regrid): per level, the octs whose state changed (new, or a
 // cell restricted again), filled bottom-up by the restriction; null: every
 // refined cell is restricted.
-ry_status finish_regrid(ry_ctx* c, const std::vector<uint8_t*>* dirty) {
+ry_status finish_regrid(ry_ctx* c, bool device, const std::vector<uint8_t*>* dirty) {
   const int nl = c->nlev, nv = c->dom.nv;
   ry_status s;
-  dfree(c, c->d_part);
-  dfree(c, c->d_segoff);
   c->seg_off.assign(1, 0);
   for (int k = 0; k < nl; ++k) c->seg_off.push_back(c->seg_off.back() + part_slots(c->lev[k]));
-  c->d_part = static_cast<double*>(dalloc(c, sizeof(double) * std::max<int64_t>(c->seg_off.back(), 1)));
-  c->d_segoff = static_cast<int64_t*>(dalloc(c, sizeof(int64_t) * c->seg_off.size()));
-  if (!c->d_part || !c->d_segoff) {
-    free_all(c);
-    c->built = false;
-    return fail(c, RY_ENOMEM, "regrid allocation failed; the context must be rebuilt");
+  if (c->seg_off.back() > c->part_cap) {
+    dfree(c, c->d_part);
+    // an eighth more than asked for: the mesh changes by a few percent
+    c->part_cap = c->seg_off.back() + c->seg_off.back() / 8;
+    c->d_part = static_cast<double*>(dalloc(c, sizeof(double) * c->part_cap));
+    if (!c->d_part) {
+      free_all(c);
+      c->built = false;
+      return fail(c, RY_ENOMEM, "regrid allocation failed; the context must be rebuilt");
+    }
   }
   HIPCHK(c, hipMemcpyAsync(c->d_segoff, c->seg_off.data(), sizeof(int64_t) * c->seg_off.size(),
                            hipMemcpyHostToDevice, c->stream));
@@ -1059,7 +1057,8 @@ ry_status finish_regrid(ry_ctx* c, const std::vector<uint8_t*>* dirty) {
     if (rc) return fail(c, RY_EHIP, "restrict kernel");
   }
   drop_graphs(c);
-  drop_super(c);
+  // the device regrid keeps the base level's tiles, and so their super-tiles
+  for (int k = device ? 1 : 0; k < nl; ++k) free_super(c, c->lev[k]);
   std::fill(std::begin(c->count), std::end(c->count), 0);
   c->slots_valid = c->smax_valid = c->chain_valid = false;
   if ((s = build_ghost_read(c))) return s;
@@ -1090,7 +1089,6 @@ ry_status regrid_device(ry_ctx* c, int64_t* n_created, int64_t* n_destroyed) {
     uint64_t* key = nullptr;
     int32_t* oc = nullptr;
     int32_t* parent = nullptr;
-    uint8_t* flag = nullptr;
     int32_t* child = nullptr;
     int32_t* tab = nullptr;
     uint32_t* tflag = nullptr;
@@ -1104,7 +1102,6 @@ ry_status regrid_device(ry_ctx* c, int64_t* n_created, int64_t* n_destroyed) {
   };
   std::vector<NewLevel> N(nl);
   std::vector<unsigned long long*> H(nl, nullptr);   // position hash of each new level
-  std::vector<std::vector<LevelView>> coarse_views;   // host sources of async copies, kept to the end
   std::vector<uint64_t> HE(nl, 0);                    // its entries
   std::vector<void*> fresh, temps;   // new level arrays / scratch of this call
   bool ok = true;
@@ -1166,39 +1163,29 @@ ry_status regrid_device(ry_ctx* c, int64_t* n_created, int64_t* n_destroyed) {
     return v;
   };
   // exclusive scan of n counts; returns the total (stream synchronised)
+  int32_t* const h_total = c->h_rb->rg.total;
   auto scan_total = [&](const int32_t* in, int32_t* out, int64_t n, int64_t& total) -> bool {
-    const int nt = scan_tmp_ints(n);
-    int32_t* tmp = static_cast<int32_t*>(A(sizeof(int32_t) * nt, true));
-    if (!tmp || launch_scan(in, out, n, tmp, st)) return false;
-    int32_t h = 0;
-    if (hipMemcpyAsync(&h, tmp + nt - 1, sizeof h, hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
-      return false;
-    total = h;
+    int32_t* tmp = static_cast<int32_t*>(A(sizeof(int32_t) * scan_tmp_ints(n), true));
+    if (!tmp || launch_scan(in, out, n, tmp, h_total, st) || hipStreamSynchronize(st) != hipSuccess) return false;
+    total = h_total[0];
     return true;
   };
   // two exclusive scans of n counts and both totals in one round trip
   auto scan_totals = [&](const int32_t* in1, int32_t* out1, const int32_t* in2, int32_t* out2, int64_t n,
                          int64_t& total1, int64_t& total2) -> bool {
-    const int nt = scan_tmp_ints(n);
-    int32_t* tmp1 = static_cast<int32_t*>(A(sizeof(int32_t) * nt, true));
-    int32_t* tmp2 = static_cast<int32_t*>(A(sizeof(int32_t) * nt, true));
-    if (!tmp1 || !tmp2 || launch_scan(in1, out1, n, tmp1, st) || launch_scan(in2, out2, n, tmp2, st)) return false;
-    int32_t h[2] = {0, 0};
-    if (hipMemcpyAsync(&h[0], tmp1 + nt - 1, sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipMemcpyAsync(&h[1], tmp2 + nt - 1, sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess ||
+    int32_t* tmp = static_cast<int32_t*>(A(sizeof(int32_t) * 2 * scan_tmp_ints(n), true));
+    if (!tmp || launch_scans({{in1, in2}, {out1, out2}}, 2, n, tmp, h_total, st) ||
         hipStreamSynchronize(st) != hipSuccess)
       return false;
-    total1 = h[0];
-    total2 = h[1];
+    total1 = h_total[0];
+    total2 = h_total[1];
     return true;
   };
-  int32_t* d_err = static_cast<int32_t*>(A(sizeof(int32_t), true));
-  // per level: children of the new level found in the old one
-  auto* d_kept = static_cast<unsigned long long*>(A(sizeof(unsigned long long) * nl, true));
-  RG_TRY(ok && hipMemsetAsync(d_err, 0, sizeof(int32_t), st) == hipSuccess &&
-             hipMemsetAsync(d_kept, 0, sizeof(unsigned long long) * nl, st) == hipSuccess,
-         RY_ENOMEM, "allocation failed");
+  // per level: children of the new level found in the old one; then the
+  // error word
+  auto* d_kept = static_cast<unsigned long long*>(A(sizeof(unsigned long long) * (nl + 1), true));
+  RG_TRY(ok && !launch_zero_u64(d_kept, nl + 1, st), RY_ENOMEM, "allocation failed");
+  int32_t* d_err = reinterpret_cast<int32_t*>(d_kept + nl);
   std::vector<int64_t> n_new(nl, 0), n_prev(nl, 0);   // child level sizes, new and old
 
   {  // level lmin keeps its octs and tile tables (a complete level: no ghost octs)
@@ -1272,24 +1259,22 @@ ry_status regrid_device(ry_ctx* c, int64_t* n_created, int64_t* n_destroyed) {
         RG_TRY(ok, RY_ENOMEM, "allocation failed");
         RG_TRY(!launch_missing_list(V, first, L.n_tile, miss, midx, mpos, mentry, st) &&
                    !launch_ghost_numbering(mpos, mentry, nm, hkey, hval, hsize, owner, gidx, gtmp, L.n, L.tab, gpos,
-                                           st),
+                                           h_total, st),
                RY_EHIP, "ghost numbering kernels");
-        int32_t h = 0;
-        RG_TRY(hipMemcpyAsync(&h, gtmp + ntmp - 1, sizeof h, hipMemcpyDeviceToHost, st) == hipSuccess &&
-                   hipStreamSynchronize(st) == hipSuccess,
-               RY_EHIP, "ghost count");
-        L.n_ghost = h;
+        RG_TRY(hipStreamSynchronize(st) == hipSuccess, RY_EHIP, "ghost count");
+        L.n_ghost = h_total[0];
       }
+      // the ghost octs' refined bytes are cleared with their sources, the
+      // octs' own are the flags
+      L.refined = static_cast<uint8_t*>(A(L.n + L.n_ghost, false));
+      RG_TRY(ok, RY_ENOMEM, "allocation failed");
       if (L.n_ghost > 0) {
-        coarse_views.emplace_back(k);
-        std::vector<LevelView>& cv = coarse_views.back();
-        for (int j = 0; j < k; ++j) cv[j] = view(k - 1 - j);
-        LevelView* d_cv = static_cast<LevelView*>(A(sizeof(LevelView) * k, true));
+        LevelViews cv{};
+        for (int j = 0; j < k; ++j) cv.v[j] = view(k - 1 - j);
         L.gsrc = static_cast<int64_t*>(A(sizeof(int64_t) * 7 * L.n_ghost, false));
         RG_TRY(ok, RY_ENOMEM, "allocation failed");
-        RG_TRY(hipMemcpyAsync(d_cv, cv.data(), sizeof(LevelView) * k, hipMemcpyHostToDevice, st) == hipSuccess &&
-                   !launch_ghost_sources(d_cv, k, RD, gpos, L.n_ghost, L.gsrc, d_err, st),
-               RY_EHIP, "ghost source kernel");
+        RG_TRY(!launch_ghost_sources(cv, k, RD, gpos, L.n_ghost, L.gsrc, L.refined + L.n, d_err, st), RY_EHIP,
+               "ghost source kernel");
       }
       // state: kept octs copied, new octs interpolated from level l-1
       const int64_t n_ext = L.n + L.n_ghost;
@@ -1312,7 +1297,7 @@ ry_status regrid_device(ry_ctx* c, int64_t* n_created, int64_t* n_destroyed) {
     }
     // flags of level l from its new state, the child level, its remap sources
     int64_t n_fine = 0;
-    L.flag = static_cast<uint8_t*>(A(L.n, true));
+    if (k == 0) L.refined = static_cast<uint8_t*>(A(L.n, false));   // no ghost octs
     RG_TRY(ok, RY_ENOMEM, "allocation failed");
     if (k + 1 < nl) {
       int32_t* cnt = static_cast<int32_t*>(A(sizeof(int32_t) * L.n, true));
@@ -1323,7 +1308,7 @@ ry_status regrid_device(ry_ctx* c, int64_t* n_created, int64_t* n_destroyed) {
       // child octs and child tiles (parents with children): both counts in
       // one round trip
       int64_t n_ctile = 0;
-      RG_TRY(!launch_regrid_flags(V, RD, l, L.U[0], FT, L.flag, cnt, has, st) &&
+      RG_TRY(!launch_regrid_flags(V, RD, l, L.U[0], FT, L.refined, cnt, has, st) &&
                  scan_totals(cnt, off, has, toff, L.n, n_fine, n_ctile),
              RY_EHIP, "regrid flag kernel");
       RG_TRY(n_ctile * TILE_TAB < (int64_t(1) << 31), RY_EINVAL,
@@ -1352,25 +1337,19 @@ ry_status regrid_device(ry_ctx* c, int64_t* n_created, int64_t* n_destroyed) {
         F.fresh = static_cast<uint8_t*>(A(n_fine, true));
         RG_TRY(ok, RY_ENOMEM, "allocation failed");
         const ChildTiles CT{toff, int32_t(n_ctile), F.tile_of, F.tfirst, F.fresh};
-        RG_TRY(!launch_regrid_children(V, OT, RD, c->dom.hbits0 + k + 1, L.flag, off, CT, F.key, F.oc, F.parent,
+        RG_TRY(!launch_regrid_children(V, OT, RD, c->dom.hbits0 + k + 1, L.refined, off, CT, F.key, F.oc, F.parent,
                                        L.child, src_old, src7, d_err, d_kept + k + 1, st),
                RY_EHIP, "regrid children kernel");
       }
     } else {
-      RG_TRY(hipMemsetAsync(L.flag, 0, L.n, st) == hipSuccess, RY_EHIP, "flag clear");
+      RG_TRY(hipMemsetAsync(L.refined, 0, L.n, st) == hipSuccess, RY_EHIP, "flag clear");
     }
     L.n_leaf = 8 * L.n - n_fine;
-    L.refined = static_cast<uint8_t*>(A(L.n + L.n_ghost, false));
-    RG_TRY(ok, RY_ENOMEM, "allocation failed");
-    RG_TRY(!launch_refined_ext(L.flag, L.n, L.n + L.n_ghost, L.refined, st), RY_EHIP, "refined kernel");
   }
-  int32_t herr = 0;
-  std::vector<unsigned long long> kept(nl, 0);
-  RG_TRY(hipMemcpyAsync(&herr, d_err, sizeof herr, hipMemcpyDeviceToHost, st) == hipSuccess &&
-             hipMemcpyAsync(kept.data(), d_kept, sizeof(unsigned long long) * nl, hipMemcpyDeviceToHost, st) ==
-                 hipSuccess &&
-             hipStreamSynchronize(st) == hipSuccess,
+  RG_TRY(!launch_regrid_readback(d_kept, d_err, nl, &c->h_rb->rg, st) && hipStreamSynchronize(st) == hipSuccess,
          RY_EHIP, "regrid kernels");
+  const int32_t herr = c->h_rb->rg.err;
+  const unsigned long long* kept = c->h_rb->rg.kept;
   for (int k = 1; k < nl; ++k) {
     created += n_new[k] - int64_t(kept[k]);
     destroyed += n_prev[k] - int64_t(kept[k]);
@@ -1420,7 +1399,7 @@ ry_status regrid_device(ry_ctx* c, int64_t* n_created, int64_t* n_destroyed) {
   // out of date
   std::vector<uint8_t*> dirty(nl, nullptr);
   for (int k = 1; k < nl; ++k) dirty[k] = N[k].fresh;
-  ry_status s = finish_regrid(c, c->means_valid ? &dirty : nullptr);
+  ry_status s = finish_regrid(c, true, c->means_valid ? &dirty : nullptr);
   release(temps);
   if (s) return s;
   if (n_created) *n_created = created;

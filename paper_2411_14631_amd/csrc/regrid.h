@@ -53,10 +53,16 @@ struct FlagTiles {
 };
 int launch_regrid_flags(const LevelView& L, const RegridDom& D, int l, const double* rho, const FlagTiles& T,
                         uint8_t* flag, int32_t* cnt, int32_t* has, void* stream);
-// exclusive scan of n int32 (tmp: scan_tmp_ints(n) ints; the total lands in
-// tmp[scan_tmp_ints(n) - 1])
+// Exclusive scans of n int32, one or two arrays (tmp: scan_tmp_ints(n) ints
+// each; the totals land in the last of them, and in host_total[0 .. njob)
+// when given: memory the device can write).
+struct ScanJobs {
+  const int32_t* in[2];
+  int32_t* out[2];
+};
 int scan_tmp_ints(int64_t n);
-int launch_scan(const int32_t* in, int32_t* out, int64_t n, int32_t* tmp, void* stream);
+int launch_scans(const ScanJobs& jobs, int njob, int64_t n, int32_t* tmp, int32_t* host_total, void* stream);
+int launch_scan(const int32_t* in, int32_t* out, int64_t n, int32_t* tmp, int32_t* host_total, void* stream);
 // The old tree around level C: old_of[o] the index in the old level of C's
 // oct o, or -1 when it is new (null: C's octs are the old ones, unchanged);
 // old_child the old level's child map (8 per oct: the child oct or -1; null
@@ -91,10 +97,17 @@ int launch_missing_list(const LevelView& L, const int32_t* first, int32_t n_tile
                         const int32_t* midx, uint64_t* mpos, int32_t* mentry, void* stream);
 int launch_ghost_numbering(const uint64_t* mpos, const int32_t* mentry, int64_t nm, unsigned long long* hkey,
                            int32_t* hval, uint64_t hsize, int32_t* owner, int32_t* gidx, int32_t* scan_tmp,
-                           int64_t n_oct, int32_t* tab, int32_t* gpos, void* stream);
-int launch_ghost_sources(const LevelView* coarse_dev, int ncoarse, const RegridDom& D, const int32_t* gpos,
-                         int64_t n_ghost, int64_t* gsrc, int32_t* err, void* stream);
-int launch_refined_ext(const uint8_t* flag, int64_t n, int64_t n_ext, uint8_t* out, void* stream);
+                           int64_t n_oct, int32_t* tab, int32_t* gpos, int32_t* host_total, void* stream);
+// The coarser levels of a level, the next coarser one first.
+struct LevelViews {
+  LevelView v[RY_MAX_LEVELS - 1];
+};
+// also clears the ghost octs' refined bytes (grefined)
+int launch_ghost_sources(const LevelViews& coarse, int ncoarse, const RegridDom& D, const int32_t* gpos,
+                         int64_t n_ghost, int64_t* gsrc, uint8_t* grefined, int32_t* err, void* stream);
+// Kept octs per level and the error word of a regrid, into host memory.
+int launch_regrid_readback(const unsigned long long* kept, const int32_t* err, int nl, RegridReadback* host,
+                           void* stream);
 
 // Restriction after a regrid of the fine octs marked in dirty_f only (the
 // same ordered 8-child means as launch_restrict); each marks its parent oct

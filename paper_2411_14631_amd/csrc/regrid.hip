@@ -478,9 +478,13 @@ __global__ __launch_bounds__(256) void regrid_children_kernel(LevelView C, OldTr
 }
 
 // ---------------------------------------------------------------------------
-// Exclusive scan of int32 counts (three passes: block scans, a scan of the
-// block sums, block offsets).  tmp holds nblocks + 1 ints; *total gets the
-// sum.
+// Exclusive scans of int32 counts, one or two arrays of the same length at a
+// time: block scans, then the blocks' offsets added.  Up to SCAN_BLOCK blocks
+// each block sums the block sums before its own itself; past that (a million
+// counts) a launch of its own scans them.  Per array tmp holds nblocks + 2
+// ints, the total last; the totals also go to host memory when given.
+// Bound: launches (3-5 us each against 2 us of work): two of them and no
+// copies where an array took three and its total a copy.
 // ---------------------------------------------------------------------------
 constexpr int SCAN_BLOCK = 1024;
 
@@ -510,20 +514,20 @@ __device__ __forceinline__ int32_t block_excl_scan(int32_t v, int32_t* total) {
   return incl - v + ws[w];
 }
 
-__global__ __launch_bounds__(SCAN_BLOCK) void scan_blocks_kernel(const int32_t* __restrict__ in,
-                                                                 int32_t* __restrict__ out, int64_t n,
-                                                                 int32_t* __restrict__ bsum) {
+__global__ __launch_bounds__(SCAN_BLOCK) void scan_blocks_kernel(ScanJobs J, int64_t n, int nb,
+                                                                 int32_t* __restrict__ tmp) {
   __shared__ int32_t tot;
   const int64_t i = int64_t(blockIdx.x) * SCAN_BLOCK + threadIdx.x;
-  const int32_t v = (i < n) ? in[i] : 0;
+  const int32_t v = (i < n) ? J.in[blockIdx.y][i] : 0;
   const int32_t e = block_excl_scan(v, &tot);
-  if (i < n) out[i] = e;
-  if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
+  if (i < n) J.out[blockIdx.y][i] = e;
+  if (threadIdx.x == 0) tmp[blockIdx.y * (nb + 2) + blockIdx.x] = tot;
 }
 
-__global__ __launch_bounds__(SCAN_BLOCK) void scan_sums_kernel(int32_t* __restrict__ bsum, int nb,
-                                                               int32_t* __restrict__ total) {
+__global__ __launch_bounds__(SCAN_BLOCK) void scan_sums_kernel(int32_t* __restrict__ tmp, int nb,
+                                                               int32_t* host_total) {
   __shared__ int32_t tot;
+  int32_t* bsum = tmp + blockIdx.y * (nb + 2);
   int32_t carry = 0;
   for (int b0 = 0; b0 < nb; b0 += SCAN_BLOCK) {
     const int i = b0 + threadIdx.x;
@@ -534,13 +538,32 @@ __global__ __launch_bounds__(SCAN_BLOCK) void scan_sums_kernel(int32_t* __restri
     carry += tot;
     __syncthreads();
   }
-  if (threadIdx.x == 0) *total = carry;
+  if (threadIdx.x == 0) {
+    bsum[nb + 1] = carry;
+    if (host_total) host_total[blockIdx.y] = carry;
+  }
 }
 
-__global__ __launch_bounds__(SCAN_BLOCK) void scan_add_kernel(int32_t* __restrict__ out, int64_t n,
-                                                              const int32_t* __restrict__ bsum) {
+// sums_scanned: tmp holds the blocks' offsets; else their sums, and the last
+// block writes the total.
+__global__ __launch_bounds__(SCAN_BLOCK) void scan_add_kernel(ScanJobs J, int64_t n, int nb, int32_t* __restrict__ tmp,
+                                                              int sums_scanned, int32_t* host_total) {
+  __shared__ int32_t tot;
   const int64_t i = int64_t(blockIdx.x) * SCAN_BLOCK + threadIdx.x;
-  if (i < n) out[i] += bsum[blockIdx.x];
+  int32_t* bsum = tmp + blockIdx.y * (nb + 2);
+  int32_t off;
+  if (sums_scanned) {
+    off = bsum[blockIdx.x];
+  } else {
+    const int32_t own = bsum[blockIdx.x];
+    (void)block_excl_scan(threadIdx.x < blockIdx.x ? bsum[threadIdx.x] : 0, &tot);
+    off = tot;
+    if (int(blockIdx.x) == nb - 1 && threadIdx.x == 0) {
+      bsum[nb + 1] = off + own;
+      if (host_total) host_total[blockIdx.y] = off + own;
+    }
+  }
+  if (i < n) J.out[blockIdx.y][i] += off;
 }
 
 // ---------------------------------------------------------------------------
@@ -664,11 +687,13 @@ __global__ void ghost_assign_kernel(const uint64_t* __restrict__ mpos, const int
 // finest level <= l-1 covering Q's neighbour: (levels up << 48) | cell.
 // Sources that cannot exist under the neighbour rule are reported in err and
 // replaced by cell 0 of level l-1, so that later reads stay in bounds.
-__global__ void ghost_source_kernel(const LevelView* __restrict__ coarse, int ncoarse, RegridDom D,
+__global__ void ghost_source_kernel(LevelViews coarse_views, int ncoarse, RegridDom D,
                                     const int32_t* __restrict__ gpos, int64_t n_ghost, int64_t* __restrict__ gsrc,
-                                    int32_t* __restrict__ err) {
+                                    uint8_t* __restrict__ grefined, int32_t* __restrict__ err) {
   const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (g >= n_ghost) return;
+  const LevelView* coarse = coarse_views.v;
+  grefined[g] = 0;
   const int64_t qx = gpos[3 * g], qy = gpos[3 * g + 1], qz = gpos[3 * g + 2];   // a cell of level l-1
   const int64_t q = cell_at(coarse[0], D.bc, qx, qy, qz);
   if (q < 0) atomicOr(err, 2);
@@ -695,15 +720,18 @@ __global__ void ghost_source_kernel(const LevelView* __restrict__ coarse, int nc
     }
 }
 
-__global__ void refined_ext_kernel(const uint8_t* __restrict__ flag, int64_t n, int64_t n_ext,
-                                   uint8_t* __restrict__ out) {
+// An empty ghost hash: keys all ones, values the largest index.
+__global__ void clear_hash_kernel(unsigned long long* hkey, int32_t* hval, int64_t n) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n_ext) out[i] = (i < n) ? flag[i] : uint8_t(0);
+  if (i >= n) return;
+  hkey[i] = ~0ull;
+  hval[i] = 0x7fffffff;
 }
-
-__global__ void fill_i32_kernel(int32_t* p, int64_t n, int32_t v) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
+__global__ void regrid_readback_kernel(const unsigned long long* __restrict__ kept, const int32_t* __restrict__ err,
+                                       int nl, RegridReadback* host) {
+  const int i = threadIdx.x;
+  if (i < nl) host->kept[i] = kept[i];
+  if (i == RY_MAX_LEVELS) host->err = *err;
 }
 __global__ void fill_u64_kernel(unsigned long long* p, int64_t n, unsigned long long v) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -744,18 +772,22 @@ int launch_pos_hash(const uint64_t* key, const int32_t* oc, int64_t n, unsigned 
 
 int scan_tmp_ints(int64_t n) { return int((n + SCAN_BLOCK - 1) / SCAN_BLOCK) + 2; }
 
-int launch_scan(const int32_t* in, int32_t* out, int64_t n, int32_t* tmp, void* stream) {
+int launch_scans(const ScanJobs& J, int njob, int64_t n, int32_t* tmp, int32_t* host_total, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   const int nb = int((n + SCAN_BLOCK - 1) / SCAN_BLOCK);
-  int32_t* total = tmp + nb + 1;
-  if (n == 0) {
-    hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(1), 0, s, total, int64_t(1), int32_t(0));
+  if (n == 0) {   // the totals alone
+    hipLaunchKernelGGL(scan_sums_kernel, dim3(1, njob), dim3(SCAN_BLOCK), 0, s, tmp, 0, host_total);
     return hipGetLastError() == hipSuccess ? 0 : -1;
   }
-  hipLaunchKernelGGL(scan_blocks_kernel, dim3(nb), dim3(SCAN_BLOCK), 0, s, in, out, n, tmp);
-  hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(SCAN_BLOCK), 0, s, tmp, nb, total);
-  hipLaunchKernelGGL(scan_add_kernel, dim3(nb), dim3(SCAN_BLOCK), 0, s, out, n, tmp);
+  hipLaunchKernelGGL(scan_blocks_kernel, dim3(nb, njob), dim3(SCAN_BLOCK), 0, s, J, n, nb, tmp);
+  const int scanned = nb > SCAN_BLOCK ? 1 : 0;
+  if (scanned) hipLaunchKernelGGL(scan_sums_kernel, dim3(1, njob), dim3(SCAN_BLOCK), 0, s, tmp, nb, host_total);
+  hipLaunchKernelGGL(scan_add_kernel, dim3(nb, njob), dim3(SCAN_BLOCK), 0, s, J, n, nb, tmp, scanned, host_total);
   return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_scan(const int32_t* in, int32_t* out, int64_t n, int32_t* tmp, int32_t* host_total, void* stream) {
+  return launch_scans({{in, nullptr}, {out, nullptr}}, 1, n, tmp, host_total, stream);
 }
 
 int launch_regrid_children(const LevelView& C, const OldTree& T, const RegridDom& D, int fbits,
@@ -788,32 +820,31 @@ int launch_missing_list(const LevelView& L, const int32_t* first, int32_t n_tile
 
 int launch_ghost_numbering(const uint64_t* mpos, const int32_t* mentry, int64_t nm, unsigned long long* hkey,
                            int32_t* hval, uint64_t hsize, int32_t* owner, int32_t* gidx, int32_t* scan_tmp,
-                           int64_t n_oct, int32_t* tab, int32_t* gpos, void* stream) {
+                           int64_t n_oct, int32_t* tab, int32_t* gpos, int32_t* host_total, void* stream) {
   if (nm == 0) return 0;
   hipStream_t s = (hipStream_t)stream;
   const uint64_t mask = hsize - 1;
-  hipLaunchKernelGGL(fill_u64_kernel, dim3(blocks(int64_t(hsize))), dim3(256), 0, s, hkey, int64_t(hsize), ~0ull);
-  hipLaunchKernelGGL(fill_i32_kernel, dim3(blocks(int64_t(hsize))), dim3(256), 0, s, hval, int64_t(hsize),
-                     int32_t(0x7fffffff));
+  hipLaunchKernelGGL(clear_hash_kernel, dim3(blocks(int64_t(hsize))), dim3(256), 0, s, hkey, hval, int64_t(hsize));
   hipLaunchKernelGGL(hash_insert_kernel, dim3(blocks(nm)), dim3(256), 0, s, mpos, nm, hkey, hval, mask);
   hipLaunchKernelGGL(owner_kernel, dim3(blocks(nm)), dim3(256), 0, s, mpos, nm, hkey, hval, mask, owner);
-  if (launch_scan(owner, gidx, nm, scan_tmp, stream)) return -1;
+  if (launch_scan(owner, gidx, nm, scan_tmp, host_total, stream)) return -1;
   hipLaunchKernelGGL(ghost_assign_kernel, dim3(blocks(nm)), dim3(256), 0, s, mpos, mentry, nm, hkey, hval, mask,
                      owner, gidx, n_oct, tab, gpos);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_ghost_sources(const LevelView* coarse_dev, int ncoarse, const RegridDom& D, const int32_t* gpos,
-                         int64_t n_ghost, int64_t* gsrc, int32_t* err, void* stream) {
+int launch_ghost_sources(const LevelViews& coarse, int ncoarse, const RegridDom& D, const int32_t* gpos,
+                         int64_t n_ghost, int64_t* gsrc, uint8_t* grefined, int32_t* err, void* stream) {
   if (n_ghost == 0) return 0;
-  hipLaunchKernelGGL(ghost_source_kernel, dim3(blocks(n_ghost)), dim3(256), 0, (hipStream_t)stream, coarse_dev,
-                     ncoarse, D, gpos, n_ghost, gsrc, err);
+  if (ncoarse < 1 || ncoarse >= RY_MAX_LEVELS) return -1;
+  hipLaunchKernelGGL(ghost_source_kernel, dim3(blocks(n_ghost)), dim3(256), 0, (hipStream_t)stream, coarse, ncoarse, D,
+                     gpos, n_ghost, gsrc, grefined, err);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_refined_ext(const uint8_t* flag, int64_t n, int64_t n_ext, uint8_t* out, void* stream) {
-  if (n_ext == 0) return 0;
-  hipLaunchKernelGGL(refined_ext_kernel, dim3(blocks(n_ext)), dim3(256), 0, (hipStream_t)stream, flag, n, n_ext, out);
+int launch_regrid_readback(const unsigned long long* kept, const int32_t* err, int nl, RegridReadback* host,
+                           void* stream) {
+  hipLaunchKernelGGL(regrid_readback_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, kept, err, nl, host);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -280,7 +280,13 @@ struct FinalizeArgs {
 int launch_finalize(const FinalizeArgs& a, void* stream);
 // What a synchronising call reads back: written into pinned host memory by
 // one kernel at the end of the stream's work.
+struct RegridReadback {
+  unsigned long long kept[RY_MAX_LEVELS];
+  int32_t err;
+  int32_t total[2];
+};
 struct Readback {
+  RegridReadback rg;
   int32_t flags[4];
   double t;
   double smax[RY_MAX_LEVELS];
