@@ -14,6 +14,7 @@
 
 #include "ry_internal.h"
 #include "regrid.h"
+#include "staging.h"
 
 using namespace ry;
 
@@ -85,6 +86,7 @@ struct ry_ctx {
   // the stream's last work left them: written into pinned host memory by one
   // small kernel ahead of a synchronisation
   Readback* h_rb = nullptr;
+  Staging staging;                        // pinned buffers of the downloads
   unsigned long long* d_floors = nullptr;
   unsigned int* d_queue = nullptr;        // 8 counters, QUEUE_STRIDE apart
   double* d_partial = nullptr;
@@ -420,8 +422,9 @@ ry_status chain_begin(ry_ctx* c, double t) {
   return RY_OK;
 }
 
+// End of a chained run (a batch's; one box's is part of its readback).
 ry_status chain_end(ry_ctx* c, int phase) {
-  if (launch_chain_end(c->d_cslots, c->d_crec, c->batch ? c->nbox : 1, phase, c->d_t, nstep_ptr(c), c->stream))
+  if (c->batch && launch_chain_end(c->d_cslots, c->d_crec, c->nbox, phase, c->d_t, nstep_ptr(c), c->stream))
     return fail(c, RY_EHIP, "chain kernel");
   c->chain_valid = true;
   c->smax_valid = c->slots_valid = false;
@@ -714,8 +717,11 @@ ry_status enqueue_coarse_step(ry_ctx* c, double t_end, int phase) {
 
 // Waits for the stream; *h_rb then holds the device's scalars, and an error
 // latched on the device is reported.
-ry_status sync_and_check(ry_ctx* c) {
-  if (launch_readback(c->d_flags, c->d_t, c->d_smax, c->batch ? 0 : c->nlev, c->d_tot, c->h_rb, c->stream))
+// chain_phase >= 0: one box's chained run ends here, at that phase.
+ry_status sync_and_check(ry_ctx* c, int chain_phase = -1) {
+  const bool end = chain_phase >= 0;
+  if (launch_readback(c->d_flags, c->d_t, c->d_smax, c->batch ? 0 : c->nlev, c->d_tot, end ? c->d_cslots : nullptr,
+                      end ? c->d_crec : nullptr, end ? chain_phase : 0, c->h_rb, c->stream))
     return fail(c, RY_EHIP, "readback kernel");
   HIPCHK(c, hipStreamSynchronize(c->stream));
   if (c->timing) time_collect(c);
@@ -750,11 +756,21 @@ void upload_level_topology(ry_ctx* c, DevLevel& D, const HostLevel& H, bool& ok)
   D.doc = upload_vec(c, oc, ok);
 }
 
+// Into the first buffer from the host (one copy where the planes have no
+// ghost octs between them), then into the second on the device.
 ry_status upload_level_state(ry_ctx* c, DevLevel& D, const double* U_host) {
-  for (int b = 0; b < 2; ++b)
-    for (int v = 0; v < c->dom.nv; ++v)
-      HIPCHK(c, hipMemcpyAsync(D.U[b] + v * D.plane(), U_host + size_t(v) * 8 * D.n_oct,
-                               sizeof(double) * 8 * D.n_oct, hipMemcpyHostToDevice, c->stream));
+  const size_t row = sizeof(double) * 8 * D.n_oct;
+  const int nv = c->dom.nv;
+  if (D.n_ghost == 0) {
+    HIPCHK(c, hipMemcpyAsync(D.U[0], U_host, row * nv, hipMemcpyHostToDevice, c->stream));
+  } else {
+    for (int v = 0; v < nv; ++v)
+      HIPCHK(c, hipMemcpyAsync(D.U[0] + v * D.plane(), U_host + size_t(v) * 8 * D.n_oct, row, hipMemcpyHostToDevice,
+                               c->stream));
+  }
+  for (int v = 0; v < nv; ++v)
+    if (launch_copy(D.U[0] + v * D.plane(), D.U[1] + v * D.plane(), 8 * D.n_oct, c->stream))
+      return fail(c, RY_EHIP, "copy kernel");
   return RY_OK;
 }
 
@@ -810,6 +826,7 @@ void ry_destroy(ry_ctx* c) {
   free_all(c);
   if (c->own_stream && c->stream) hipStreamDestroy(c->stream);
   if (c->h_rb) hipHostFree(c->h_rb);
+  c->staging.release();
   for (auto& tl : c->pending) {
     hipEventDestroy(tl.a);
     hipEventDestroy(tl.b);
@@ -1600,7 +1617,7 @@ ry_status ry_advance(ry_ctx* c, int32_t n_coarse, double t_end, double* t_io) {
     c->slots_valid = true;
     c->smax_valid = c->chain_valid = false;
   }
-  if ((s = sync_and_check(c))) return s;
+  if ((s = sync_and_check(c, chained ? phase : -1))) return s;
   const int32_t nrun = c->h_rb->flags[2];
   if (nrun < 0 || nrun > n_coarse) return fail(c, RY_EHIP, "device step count %d out of range", nrun);
   c->lev[0].cur = cur0 ^ (nrun & 1);
@@ -1635,9 +1652,9 @@ ry_status ry_download(ry_ctx* c, int32_t level, double* U) {
   RY_ABI_TRY
   if (!c || !U || !c->built || c->batch || level < c->cfg.level_min || level > c->cfg.level_max) return RY_EINVAL;
   DevLevel& D = c->lev[level - c->cfg.level_min];
-  for (int v = 0; v < c->dom.nv && D.n_oct; ++v)
-    HIPCHK(c, hipMemcpyAsync(U + size_t(v) * 8 * D.n_oct, D.U[D.cur] + v * D.plane(), sizeof(double) * 8 * D.n_oct,
-                             hipMemcpyDeviceToHost, c->stream));
+  if (D.n_oct)
+    HIPCHK(c, c->staging.download(U, D.U[D.cur], sizeof(double) * 8 * D.n_oct, sizeof(double) * D.plane(), c->dom.nv,
+                                  c->stream));
   return sync_and_check(c);
   RY_ABI_CATCH
 }
@@ -1878,9 +1895,8 @@ ry_status ry_batch_download(ry_ctx* c, int32_t box, double* U) {
   if (!c || !c->batch || !U || box < 0 || box >= c->nbox) return RY_EINVAL;
   DevLevel& D = c->lev[0];
   const int64_t n = c->box_noct[box];
-  for (int v = 0; v < NVAR; ++v)
-    HIPCHK(c, hipMemcpyAsync(U + size_t(v) * 8 * n, D.U[D.cur] + v * D.plane() + c->box_off[box] * 8,
-                             sizeof(double) * 8 * n, hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(c, c->staging.download(U, D.U[D.cur] + c->box_off[box] * 8, sizeof(double) * 8 * n,
+                                sizeof(double) * D.plane(), NVAR, c->stream));
   return sync_and_check(c);
   RY_ABI_CATCH
 }

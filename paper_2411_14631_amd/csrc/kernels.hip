@@ -465,15 +465,26 @@ __global__ void begin_kernel(double t, double* d_t, int32_t* flags) {
   *d_t = t;
   flags[0] = flags[1] = flags[2] = 0;
 }
-__global__ __launch_bounds__(64) void readback_kernel(const int32_t* __restrict__ flags, const double* __restrict__ t,
-                                                      const double* __restrict__ smax, int nsmax,
-                                                      const double* __restrict__ tot, Readback* host) {
+// slots: the end of a chained run of one box at `phase` as well
+// (chain_end_kernel's work).
+__global__ __launch_bounds__(64) void readback_kernel(int32_t* flags, double* t, const double* __restrict__ smax,
+                                                      int nsmax, const double* __restrict__ tot,
+                                                      unsigned long long* slots, const StepRec* __restrict__ rec,
+                                                      int phase, Readback* host) {
   const int i = threadIdx.x;
-  if (i < 4) host->flags[i] = flags[i];
-  if (i == 4) host->t = *t;
+  if (slots) {
+    if (phase) slots[i] = slots[phase * CHAIN_SLOTS + i];
+    if (i == 4) *t = host->t = rec[phase].t;
+    if (i == 2) flags[2] = host->flags[2] = rec[phase].nstep;
+  } else {
+    if (i == 4) host->t = *t;
+    if (i == 2) host->flags[2] = flags[2];
+  }
+  if (i < 4 && i != 2) host->flags[i] = flags[i];
   if (i >= 8 && i < 8 + nsmax) host->smax[i - 8] = smax[i - 8];
   if (i >= 32 && i < 32 + NVMAX) host->tot[i - 32] = tot[i - 32];
 }
+static_assert(CHAIN_SLOTS == 64, "one lane per slot");
 static_assert(8 + RY_MAX_LEVELS <= 32 && 32 + NVMAX <= 64, "one lane per value");
 
 // Chained runs: their first and last kernel (one thread per slot).
@@ -514,9 +525,10 @@ int launch_begin(double t, double* d_t, int32_t* flags, void* stream) {
   hipLaunchKernelGGL(begin_kernel, dim3(1), dim3(1), 0, (hipStream_t)stream, t, d_t, flags);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
-int launch_readback(const int32_t* flags, const double* t, const double* smax, int nsmax, const double* tot,
-                    Readback* host, void* stream) {
-  hipLaunchKernelGGL(readback_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, flags, t, smax, nsmax, tot, host);
+int launch_readback(int32_t* flags, double* t, const double* smax, int nsmax, const double* tot,
+                    unsigned long long* slots, const StepRec* rec, int phase, Readback* host, void* stream) {
+  hipLaunchKernelGGL(readback_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, flags, t, smax, nsmax, tot, slots, rec,
+                     phase, host);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -44,6 +44,7 @@
 #include <vector>
 
 #include "../../include/ry_poisson.h"
+#include "staging.h"
 
 namespace ryp {
 
@@ -757,6 +758,7 @@ struct ry_poisson {
   Scalars* sc = nullptr;
   int32_t* h_done = nullptr;   // pinned
   int nblk = 0, cz = 0;
+  ry::Staging staging;         // pinned buffers of the downloads
   bool ready = false;          // set_rhs done
   int64_t iter = 0;            // the device's iteration index (once the stream's work is done)
   hipGraphExec_t graph[2] = {};   // by parity of the first iteration's index (two-sweep: [0])
@@ -811,6 +813,7 @@ void pfree_all(ry_poisson* p) {
     hipEventDestroy(e.second);
   }
   p->ev.clear();
+  p->staging.release();
   if (p->h_done) hipHostFree(p->h_done);
   p->h_done = nullptr;
 }
@@ -1150,7 +1153,6 @@ ry_status ry_poisson_download(ry_poisson* p, int32_t which, double* host) {
       slot = which == RY_PV_Q ? s2 : s1;
     }
     PCHK(p, hipGetLastError());
-    PCHK(p, hipStreamSynchronize(p->stream));
   } else {
     // x r u w z q s p; w_i lives in buffer (i & 1)
     switch (which) {
@@ -1161,7 +1163,8 @@ ry_status ry_poisson_download(ry_poisson* p, int32_t which, double* host) {
       default: slot = which + 1; break;   // z q s p -> 5..8
     }
   }
-  PCHK(p, hipMemcpy(host, p->v[slot], sizeof(double) * size_t(p->N), hipMemcpyDeviceToHost));
+  const size_t bytes = sizeof(double) * size_t(p->N);
+  PCHK(p, p->staging.download(host, p->v[slot], bytes, bytes, 1, p->stream));
   return RY_OK;
   RY_ABI_CATCH
 }

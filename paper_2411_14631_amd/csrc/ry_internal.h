@@ -292,8 +292,9 @@ struct Readback {
   double smax[RY_MAX_LEVELS];
   double tot[NVMAX];
 };
-int launch_readback(const int32_t* flags, const double* t, const double* smax, int nsmax, const double* tot,
-                    Readback* host, void* stream);
+// slots, rec given: the end of a chained run of one box as well (launch_chain_end).
+int launch_readback(int32_t* flags, double* t, const double* smax, int nsmax, const double* tot,
+                    unsigned long long* slots, const StepRec* rec, int phase, Readback* host, void* stream);
 // Start of a chained run (sets [4][nbox]): phase 0's records from t (a value,
 // or per box when t_dev is given), its slots from smax (nullptr: they hold
 // the maxima already), the next two phases' slots cleared.

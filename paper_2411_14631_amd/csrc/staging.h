@@ -1,0 +1,106 @@
+// Device-to-host copies into ordinary (pageable) memory through pinned
+// chunks, by a few host threads: each asks the copy engine for a chunk and
+// moves it on while the engine serves the others.
+//
+// Bound: the copy engine (57 GB/s into pinned memory) and the host's first
+// touch of the destination (20 GB/s on one thread, hence several); the
+// runtime's own path for pageable memory reaches 12 GB/s.  Into a fresh
+// array, 10.5 MB: 855 -> 577 us; 134 MB: 13.2 -> 5.0 ms.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <atomic>
+#include <cstddef>
+#include <cstring>
+#include <system_error>
+#include <thread>
+
+namespace ry {
+
+struct Staging {
+  static constexpr size_t kChunk = size_t(1) << 20;
+  static constexpr size_t kLeast = size_t(4) << 20;     // below this the runtime's path costs less (2 MB: 153 / 172 us)
+  static constexpr int kThreads = 4;                    // the caller's and up to three more
+  char* buf = nullptr;                                  // a chunk per thread, kept for the owner's life
+  hipEvent_t ev[kThreads] = {};
+
+  // rows of `bytes` each, `stride` apart on the device, one after the other
+  // on the host; waits for the stream
+  hipError_t download(void* host, const void* dev, size_t bytes, size_t stride, int rows, hipStream_t st) {
+    const size_t total = bytes * size_t(rows);
+    int device = 0;
+    if (total < kLeast || hipGetDevice(&device) != hipSuccess || !ready()) {
+      for (int r = 0; r < rows; ++r) {
+        const hipError_t e = hipMemcpyAsync(static_cast<char*>(host) + r * bytes,
+                                            static_cast<const char*>(dev) + r * stride, bytes,
+                                            hipMemcpyDeviceToHost, st);
+        if (e != hipSuccess) return e;
+      }
+      return hipStreamSynchronize(st);
+    }
+    // chunk k: up to kChunk bytes of one row
+    const size_t per = (bytes + kChunk - 1) / kChunk, n = per * size_t(rows);
+    std::atomic<size_t> next{0};
+    std::atomic<int> error{int(hipSuccess)};
+    auto work = [&](int w) {
+      hipError_t e = w ? hipSetDevice(device) : hipSuccess;   // the device is a thread's own setting
+      char* b = buf + w * kChunk;
+      while (e == hipSuccess && error.load() == int(hipSuccess)) {
+        const size_t k = next.fetch_add(1);
+        if (k >= n) return;
+        const size_t row = k / per, off = (k % per) * kChunk, len = std::min(kChunk, bytes - off);
+        e = hipMemcpyAsync(b, static_cast<const char*>(dev) + row * stride + off, len, hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipEventRecord(ev[w], st);
+        if (e == hipSuccess) e = hipEventSynchronize(ev[w]);
+        if (e == hipSuccess) std::memcpy(static_cast<char*>(host) + row * bytes + off, b, len);
+      }
+      if (e != hipSuccess) error.store(int(e));
+    };
+    std::thread extra[kThreads - 1];
+    const int nextra = int(std::min<size_t>(kThreads - 1, n / 2));
+    for (int w = 0; w < nextra; ++w) {
+      try {
+        extra[w] = std::thread(work, w + 1);
+      } catch (const std::system_error&) {
+        break;                                           // the threads there are do the work
+      }
+    }
+    work(0);
+    for (auto& t : extra)
+      if (t.joinable()) t.join();
+    const hipError_t e = hipError_t(error.load());
+    if (e != hipSuccess) (void)hipStreamSynchronize(st);  // nothing may still write the buffers
+    return e;
+  }
+
+  void release() {
+    for (auto& x : ev) {
+      if (x) (void)hipEventDestroy(x);
+      x = nullptr;
+    }
+    if (buf) (void)hipHostFree(buf);
+    buf = nullptr;
+  }
+
+ private:
+  // the pinned chunks, on first use; without them copies take the runtime's path
+  bool ready() {
+    if (buf) return true;
+    if (hipHostMalloc(reinterpret_cast<void**>(&buf), kThreads * kChunk) != hipSuccess) {
+      buf = nullptr;
+      (void)hipGetLastError();
+      return false;
+    }
+    for (auto& x : ev)
+      if (hipEventCreateWithFlags(&x, hipEventDisableTiming) != hipSuccess) {
+        x = nullptr;
+        release();
+        (void)hipGetLastError();
+        return false;
+      }
+    return true;
+  }
+};
+
+}  // namespace ry
