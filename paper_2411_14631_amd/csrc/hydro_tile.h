@@ -562,6 +562,7 @@ struct GatherRegs {
   static constexpr int NRA = (Geom<K>::NPOS_A + NT - 1) / NT;
   double Ua[NRA][NV];
   int iwa[NRA];   // LDS index of each position, -1 when the thread has none
+  uint32_t cell[NRA];   // its cell index
 };
 
 // Last in-domain cell of a tile along each axis (a tile cut by the domain's
@@ -647,6 +648,7 @@ __device__ __forceinline__ void gather_issue(const HydroArgs& A, const int32_t* 
       // reads: it takes the (valid, finite) state of the level's first cell
       // instead of a branch
       const uint32_t cell = (e >= 0) ? uint32_t(e) * 8u + uint32_t(cb) : 0u;
+      R.cell[rnd] = cell;
       if (off32) {
         // planes under 4 GiB: one 32-bit byte offset serves every plane
         const uint32_t boff = cell << 3;
@@ -983,6 +985,13 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
 #pragma unroll
   for (int r = 0; r < NCR; ++r) {
     const int cx = cxs[r], cy = cys[r], cz = czs[r];
+    if constexpr (ONE) {
+      // every cell of the domain is a leaf cell, the thread's own one was the
+      // first position it gathered
+      leaf[r] = active && cthr && (fl == 0u || (cx <= hb[0] && cy <= hb[1] && cz <= hb[2]));
+      cell[r] = R.cell[r];
+      continue;
+    }
     const int ts = G::slot(cx >> 1, cy >> 1, cz >> 1);
     e[r] = (active && cthr) ? tab[ts] : -1;
     const int ci = (cx & 1) | ((cy & 1) << 1) | ((cz & 1) << 2);
@@ -1064,8 +1073,9 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
       }
       if (A.tile_smax || A.smax_bits || A.err) {
         const double sr = signal_speed(Un, g, rf, pf);
-        const bool bad = !(isfinite(Un[0]) && isfinite(Un[1]) && isfinite(Un[2]) && isfinite(Un[3]) &&
-                           isfinite(Un[4])) || !(Un[0] > 0.0) || !(Un[4] > 0.0) || !isfinite(sr);
+        // a non-finite density, momentum or energy gives a non-finite speed
+        // (an energy that is not a number fails its comparison)
+        const bool bad = !(Un[0] > 0.0) || !(Un[4] > 0.0) || !isfinite(sr);
         if (bad) atomicOr(A.err, 1);
         s = (r == 0) ? (bad ? 0.0 : sr) : fmax(s, bad ? 0.0 : sr);
       }

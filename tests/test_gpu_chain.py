@@ -101,3 +101,31 @@ def test_chained_batch(ry):
         h.close()
     for r in res[1:]:
         same(r, res[0])
+
+
+@pytest.mark.parametrize("n,bc", [(30, W.BC_OUTFLOW), (18, W.BC_PERIODIC), (16, W.BC_OUTFLOW), (36, W.BC_PERIODIC)])
+def test_floor_census_of_one_level(ry, n, bc):
+    """Floors raised into the field's range, so that a good part of all cells
+    and face states meet them: the chained kernels' counts (from a thread's
+    place in its tile) equal the general census and the oracle's."""
+    from oracle.ryo import Oracle
+    prob = dataclasses.replace(W.random_smooth(n, seed=11, mach=0.9), bc=(bc,) * 6, rho_floor=0.9, p_floor=0.8)
+    o = Oracle(prob)
+    o.advance(2)
+    counts, states = [], []
+    for t in (QUEUE, K4, (1, 0, 4, 1, 2, 4), (1, 0, 4, 1, 4, 4), (4, 0, 4, 1, 1, 4), K8, K84):
+        h = ry.Hydro(prob)
+        h.set_tuning(*t)
+        h.advance(2)
+        counts.append(h.floors())
+        states.append(h.download(prob.level_min))
+        h.close()
+    assert counts[0] == o.floors() > n ** 3 // 10
+    assert counts == [counts[0]] * len(counts)
+    same(states, [states[0]] * len(states))
+    m = [ry.Hydro(prob, "mixed") for _ in range(2)]
+    m[0].set_tuning(*QUEUE)
+    m[1].set_tuning(*K8)
+    for h in m:
+        h.advance(2)
+    assert m[0].floors() == m[1].floors() > 0
