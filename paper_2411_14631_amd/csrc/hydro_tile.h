@@ -73,19 +73,18 @@ struct Geom {
   static constexpr int KO = K / 2;                       // octs per tile edge
   static constexpr int TS = KO + 2;                      // oct neighbourhood edge (one oct of halo)
   static constexpr int TAB = TS * TS * TS;               // oct neighbourhood entries per tile
-  static constexpr int R = K + 4;                        // stencil positions per axis
-  // table a entry: LDS index | oct slot | in-oct cell | raw position
+  // table a entry: LDS index | oct slot | in-oct cell (the slot and the cell
+  // give the position, position_of)
   static constexpr int A_LB = (K == 4) ? 10 : 11, A_SB = (K == 4) ? 6 : 8;
-  static constexpr int A_CS = A_LB + A_SB, A_RS = A_CS + 3;
-  // table b entry (one-layer cells): cell LDS index | far-plane neighbour
-  // LDS index | normal axis | upper layer | face between the cell and the core
-  static constexpr int B_LB = (K == 4) ? 9 : 11;
+  static constexpr int A_CS = A_LB + A_SB;
+  // table b entry (one-layer cells, K = 4): cell LDS index | far-plane
+  // neighbour LDS index | normal axis | upper layer | face between the cell
+  // and the core.  K = 8: a layer is a wavefront's 64 cells, so all of it
+  // follows from the layer's number and the lane (layer_cell)
+  static constexpr int B_LB = 9;
   static constexpr int B_DS = 2 * B_LB, B_US = B_DS + 2, B_FS = B_US + 1;
-  using EntA = std::conditional_t<K == 4, uint32_t, uint64_t>;
-  using EntB = std::conditional_t<K == 4, uint32_t, uint64_t>;
-  static_assert(WSIZE < (1 << B_LB) && WSIZE < (1 << A_LB) && TAB <= (1 << A_SB), "LDS / slot fields");
-  static_assert(int64_t(R) * R * R <= (int64_t(1) << (8 * sizeof(EntA) - A_RS)), "raw position field");
-  static_assert(NFACE <= (int64_t(1) << (8 * sizeof(EntB) - B_FS)), "face field");
+  static_assert(WSIZE < (1 << A_LB) && TAB <= (1 << A_SB) && A_CS + 3 <= 32, "LDS / slot fields");
+  static_assert(K != 4 || (WSIZE < (1 << B_LB) && NFACE <= (1 << (32 - B_FS))), "one-layer fields");
 
   __host__ __device__ static constexpr int widx(int x, int y, int z) {
     return (x >= -1 && x <= K && y >= -1 && y <= K && z >= -1 && z <= K)
@@ -133,32 +132,58 @@ struct Geom {
 };
 
 // Per-item constants, computed at compile time:
-//  a[i]: LDS index, oct-table slot, in-oct cell and raw (x+2) + R (y+2) +
-//        R^2 (z+2) of stencil position i (fields as Geom<K>::A_*)
-//  b[i], i >= NCORE (one-layer cells: the upper ones at coordinate K along
+//  a[i]: LDS index, oct-table slot, in-oct cell of stencil position i (fields
+//        as Geom<K>::A_*)
+//  b[i - NCORE] (K = 4; one-layer cells: the upper ones at coordinate K along
 //        their normal, then the lower ones at -1): LDS index of the cell, LDS
 //        index of its outward neighbour (a far plane), normal axis, upper
 //        layer, the face between the cell and the core (fields as
-//        Geom<K>::B_*).  b[i < NCORE] = LDS index of core cell i (the
-//        threads' oct-major order, Geom<K>::core_x/y/z).
+//        Geom<K>::B_*)
 template <int K>
 struct StencilTables {
-  typename Geom<K>::EntA a[Geom<K>::NPOS_A];
-  typename Geom<K>::EntB b[Geom<K>::NPOS_B];
+  uint32_t a[Geom<K>::NPOS_A];
+  uint32_t b[K == 4 ? Geom<K>::NPOS_B - Geom<K>::NCORE : 1];
 };
+
+// A one-layer cell: LDS index of its primitives, of its outward neighbour's
+// (a far plane), the face between it and the core, its normal axis and
+// whether it lies on the upper side.
+struct LayerCell {
+  int iw, far, face, dn;
+  bool up;
+};
+// Its place (x, y, z in [-1, K]) from layer number (0-2 the upper layers of
+// x, y, z, 3-5 the lower ones) and position t = t1 + K t2 in the layer.
+template <int K>
+__host__ __device__ constexpr LayerCell layer_at(int layer, int t) {
+  using G = Geom<K>;
+  const bool up = layer < 3;
+  const int d = up ? layer : layer - 3, t1 = t % K, t2 = t / K;
+  const int s1 = d == 0 ? G::WB : 1, s2 = d == 2 ? G::WB : G::WBB, sd = d == 0 ? 1 : (d == 1 ? G::WB : G::WBB);
+  LayerCell c{};
+  c.iw = (1 + G::WB + G::WBB) + sd * (up ? K : -1) + s1 * t1 + s2 * t2;
+  c.far = G::NBOX + (2 * d + (up ? 1 : 0)) * K * K + t;
+  c.dn = d;
+  c.up = up;
+  if constexpr (K == 8) {
+    // fidx of the face's upper cell: the layer's 64 faces lie next to each other
+    c.face = (d == 0 ? 0 : (d == 1 ? G::FD0 : G::FD0 + G::FD1)) + (up ? K * (d == 0 ? 66 : 68) : 0) + t;
+  } else {
+    const int u = up ? K : 0;
+    c.face = d == 0 ? G::fidx(0, u, t1, t2) : (d == 1 ? G::fidx(1, t1, u, t2) : G::fidx(2, t1, t2, u));
+  }
+  return c;
+}
 
 template <int K>
 constexpr StencilTables<K> make_tables() {
   using G = Geom<K>;
-  using EA = typename G::EntA;
-  using EB = typename G::EntB;
   StencilTables<K> t{};
   int na = 0;
   auto put = [&](int x, int y, int z) {
     const int slot = G::slot(x >> 1, y >> 1, z >> 1);
     const int cb = (x & 1) | ((y & 1) << 1) | ((z & 1) << 2);
-    const int raw = (x + 2) + G::R * (y + 2) + G::R * G::R * (z + 2);
-    t.a[na++] = EA(G::widx(x, y, z)) | (EA(slot) << G::A_LB) | (EA(cb) << G::A_CS) | (EA(raw) << G::A_RS);
+    t.a[na++] = uint32_t(G::widx(x, y, z)) | (uint32_t(slot) << G::A_LB) | (uint32_t(cb) << G::A_CS);
   };
   // the core cells first, in the threads' oct-major order (a thread's first
   // gathered position is its own cell), then the halo positions oct by oct
@@ -175,26 +200,35 @@ constexpr StencilTables<K> make_tables() {
           const bool edges = (ox ? ex : true) && (oy ? ey : true) && (oz ? ez : true);
           if ((nout == 1) || (nout == 2 && edges)) put(x, y, z);
         }
-  for (int i = 0; i < G::NCORE; ++i) t.b[i] = EB(G::widx(G::core_x(i), G::core_y(i), G::core_z(i)));
-  int nb = G::NCORE;
-  for (int up = 1; up >= 0; --up)
-    for (int d = 0; d < 3; ++d)
-      for (int t2 = 0; t2 < K; ++t2)
-        for (int t1 = 0; t1 < K; ++t1) {
-          int c[3] = {0, 0, 0};
-          c[d] = up ? K : -1;
-          c[d == 0 ? 1 : 0] = t1;
-          c[d == 2 ? 1 : 2] = t2;
-          int o[3] = {c[0], c[1], c[2]};
-          o[d] += up ? 1 : -1;
-          int u[3] = {c[0], c[1], c[2]};
-          if (!up) u[d] += 1;
-          const int face = G::fidx(d, u[0], u[1], u[2]);
-          t.b[nb++] = EB(G::widx(c[0], c[1], c[2])) | (EB(G::widx(o[0], o[1], o[2])) << G::B_LB) |
-                      (EB(d) << G::B_DS) | (EB(up) << G::B_US) | (EB(face) << G::B_FS);
-        }
+  if constexpr (K == 4)
+    for (int i = 0; i < G::NPOS_B - G::NCORE; ++i) {
+      const LayerCell c = layer_at<K>(i / (K * K), i % (K * K));
+      t.b[i] = uint32_t(c.iw) | (uint32_t(c.far) << G::B_LB) | (uint32_t(c.dn) << G::B_DS) |
+               (uint32_t(c.up) << G::B_US) | (uint32_t(c.face) << G::B_FS);
+    }
   return t;
 }
+// layer_at agrees with the index functions
+template <int K>
+constexpr bool layers_right() {
+  using G = Geom<K>;
+  for (int l = 0; l < 6; ++l)
+    for (int t = 0; t < K * K; ++t) {
+      const LayerCell c = layer_at<K>(l, t);
+      int p[3] = {0, 0, 0};
+      p[c.dn] = c.up ? K : -1;
+      p[c.dn == 0 ? 1 : 0] = t % K;
+      p[c.dn == 2 ? 1 : 2] = t / K;
+      int o[3] = {p[0], p[1], p[2]}, u[3] = {p[0], p[1], p[2]};
+      o[c.dn] += c.up ? 1 : -1;
+      if (!c.up) u[c.dn] += 1;
+      if (c.iw != G::widx(p[0], p[1], p[2]) || c.far != G::widx(o[0], o[1], o[2]) ||
+          c.face != G::fidx(c.dn, u[0], u[1], u[2]))
+        return false;
+    }
+  return true;
+}
+static_assert(layers_right<4>() && layers_right<8>(), "one-layer cells");
 static __constant__ StencilTables<4> c_st4 = make_tables<4>();
 static __constant__ StencilTables<8> c_st8 = make_tables<8>();
 // every table entry filled (the position counts match the enumerations)
@@ -203,8 +237,6 @@ constexpr bool tables_full() {
   constexpr StencilTables<K> t = make_tables<K>();
   for (int i = 0; i < Geom<K>::NPOS_A; ++i)
     if (t.a[i] == 0) return false;
-  for (int i = Geom<K>::NCORE; i < Geom<K>::NPOS_B; ++i)
-    if (t.b[i] == 0) return false;
   return true;
 }
 static_assert(tables_full<4>() && tables_full<8>(), "stencil tables");
@@ -212,6 +244,31 @@ template <int K>
 __device__ __forceinline__ const StencilTables<K>& stencil_tables() {
   if constexpr (K == 4) return c_st4;
   else return c_st8;
+}
+// Position (each coordinate in [-2, K+1]) of a stencil table entry.
+template <int K>
+__device__ __forceinline__ void position_of(uint32_t ent, int& x, int& y, int& z) {
+  using G = Geom<K>;
+  const int slot = int((ent >> G::A_LB) & ((1u << G::A_SB) - 1)), cb = int((ent >> G::A_CS) & 7u);
+  x = 2 * (slot % G::TS) - 2 + (cb & 1);
+  y = 2 * ((slot / G::TS) % G::TS) - 2 + ((cb >> 1) & 1);
+  z = 2 * (slot / (G::TS * G::TS)) - 2 + (cb >> 2);
+}
+// One-layer cell i (NCORE <= i < NPOS_B); K = 4: from its table entry, K = 8:
+// from the wavefront's layer, which is uniform, and the lane -- no table
+// load, and the axis and side are scalars (the layers' part of the slopes,
+// face states and fluxes without per-lane selects).
+template <int K>
+__device__ __forceinline__ LayerCell layer_cell(uint32_t ent, int i) {
+  using G = Geom<K>;
+  if constexpr (K == 4) {
+    constexpr uint32_t M = (1u << G::B_LB) - 1;
+    return {int(ent & M), int((ent >> G::B_LB) & M), int(ent >> G::B_FS), int((ent >> G::B_DS) & 3u),
+            ((ent >> G::B_US) & 1u) != 0};
+  } else {
+    static_assert(K * K == 64 && G::NCORE % 64 == 0, "a layer per wavefront");
+    return layer_at<K>(__builtin_amdgcn_readfirstlane((i - G::NCORE) >> 6), i & 63);
+  }
 }
 
 // One LDS buffer serves three phases in turn: primitives [NVAR][WSIZE] (A,
@@ -599,10 +656,9 @@ __device__ __forceinline__ bool level_off32(const HydroArgs& A) {
 template <int K, int NT, int NV>
 __device__ __forceinline__ void gather_issue(const HydroArgs& A, const int32_t* tab, uint32_t fl, const int hb[3],
                                              int tid, bool active,
-                                             const typename Geom<K>::EntA (&entA)[GatherRegs<K, NT, NV>::NRA],
+                                             const uint32_t (&entA)[GatherRegs<K, NT, NV>::NRA],
                                              GatherRegs<K, NT, NV>& R) {
   using G = Geom<K>;
-  using EA = typename G::EntA;
   constexpr int NRA = GatherRegs<K, NT, NV>::NRA;
   const int64_t P = A.plane;
   // the planes' base addresses, formed in scalar registers (an empty asm on
@@ -624,12 +680,12 @@ __device__ __forceinline__ void gather_issue(const HydroArgs& A, const int32_t* 
     const int i = tid + NT * rnd;
     R.iwa[rnd] = -1;
     if (active && i < G::NPOS_A) {
-      const EA ent = entA[rnd];
-      int slot = int((ent >> G::A_LB) & EA((1u << G::A_SB) - 1)), cb = int((ent >> G::A_CS) & EA(7));
+      const uint32_t ent = entA[rnd];
+      int slot = int((ent >> G::A_LB) & ((1u << G::A_SB) - 1)), cb = int((ent >> G::A_CS) & 7u);
       if (fl & CL_ANY) {
         // outflow faces: clamp the position into the domain (zero gradient)
-        const int raw = int(ent >> G::A_RS);
-        int sx = raw % G::R - 2, sy = (raw / G::R) % G::R - 2, sz = raw / (G::R * G::R) - 2;
+        int sx, sy, sz;
+        position_of<K>(ent, sx, sy, sz);
         if ((fl & CL_LOX) && sx < 0) sx = 0;
         if ((fl & CL_HIX) && sx > hb[0]) sx = hb[0];
         if ((fl & CL_LOY) && sy < 0) sy = 0;
@@ -642,7 +698,7 @@ __device__ __forceinline__ void gather_issue(const HydroArgs& A, const int32_t* 
       int32_t e = tab[slot];
       if (!debug_in_bounds(e < A.n_oct || (e >= A.n_oct + A.ghost_adj && e < A.n_ext + A.ghost_adj), A.err))
         e = -1;
-      R.iwa[rnd] = int(ent & EA((1u << G::A_LB) - 1));
+      R.iwa[rnd] = int(ent & ((1u << G::A_LB) - 1));
       // 32-bit cell index (a level's octs, ghost octs and the ghost shift
       // stay below 2^29 octs).  A slot without an oct is one no leaf update
       // reads: it takes the (valid, finite) state of the level's first cell
@@ -675,8 +731,6 @@ template <typename Real, int NT, int NS, int K, bool ONE>
 __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS<Real, NVAR + NS, K>& S, int tid_in,
                                            bool active, GatherRegs<K, NT, NVAR + NS>& R) {
   using G = Geom<K>;
-  using EA = typename G::EntA;
-  using EB = typename G::EntB;
   constexpr int NV = NVAR + NS;
   constexpr int WSIZE = G::WSIZE, NFACE = G::NFACE, NUPPER = G::NUPPER, NCORE = G::NCORE;
   constexpr int NPOS_A = G::NPOS_A, NPOS_B = G::NPOS_B, TAB = G::TAB;
@@ -717,14 +771,14 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
   static_assert(2 * (SITE_R + 3 * NCR) <= 64, "floor sites");
   using Pend = std::conditional_t<(2 * (SITE_R + 3 * NCR) <= 32), uint32_t, uint64_t>;
   Pend pending = 0;
-  EB entB[NRB];
+  uint32_t entB[NRB];
 #pragma unroll
   for (int rnd = 0; rnd < NRB; ++rnd) {
     const int i = tid + NT * rnd;
-    entB[rnd] = ST.b[uint32_t(i < NPOS_B ? i : 0)];
+    entB[rnd] = K == 4 ? ST.b[uint32_t(i >= NCORE && i < NPOS_B ? i - NCORE : 0)] : 0u;
   }
 
-  EA entA[NRA];
+  uint32_t entA[NRA];
 #pragma unroll
   for (int rnd = 0; rnd < NRA; ++rnd) {
     const int i = tid + NT * rnd;
@@ -824,14 +878,14 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
     czs[r] = G::core_z(ct);
   }
   const Real rfr = Real(rf), pfr = Real(pf), gr = Real(g);
-  constexpr EB LMASK = EB((1u << G::B_LB) - 1);
   Real Pw[NCR][NV], Pd[NCR][3][NV];
   Real Ls[NRB][NV];
-  EB Lb[NRB];
+  // the thread's one-layer cell of a round (K = 8: formed again in each
+  // phase from the wavefront's number and the lane, not held in registers)
+  auto layer_of = [&](int rnd) { return layer_cell<K>(entB[rnd], (K == 8 ? opaque(tid) : tid) + NT * rnd); };
 #pragma unroll
   for (int rnd = 0; rnd < NRB; ++rnd) {
     const int i = tid + NT * rnd;
-    Lb[rnd] = 0u;
     if (!active || i >= NPOS_B) continue;
     if (rnd < NCR && core) {
       const int r = rnd < NCR ? rnd : 0;
@@ -848,10 +902,9 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
       const Real ir = (sizeof(Real) == 8) ? Real(irc[r]) : rcp(W0[0]);
       predict<Real, NS>(W0, Pd[r], h, gr, Pw[r], ir);
     } else {
-      const EB e = entB[rnd];
-      Lb[rnd] = e;
-      const int iw = int(e & LMASK), far = int((e >> G::B_LB) & LMASK), dn = int((e >> G::B_DS) & EB(3));
-      const bool up = (e >> G::B_US) & EB(1);
+      const LayerCell lc = layer_of(rnd);
+      const int iw = lc.iw, far = lc.far, dn = lc.dn;
+      const bool up = lc.up;
       Real W0[NV], D[3][NV], Q[NV];
 #pragma unroll
       for (int v = 0; v < NV; ++v) W0[v] = W[v * WSIZE + iw];
@@ -863,12 +916,22 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
         for (int v = 0; v < NV; ++v) D[d][v] = mmod(W0[v] - W[v * WSIZE + lo], W[v * WSIZE + hi] - W0[v]);
       }
       predict<Real, NS>(W0, D, h, gr, Q, rcp(W0[0]));
-      // the face state Q +- D/2 along the normal: the weights of the two other
-      // axes are zero, so their fused terms add exact zeros
+      // the face state Q +- D/2 along the normal
       const Real sg = up ? Real(-0.5) : Real(0.5);
-      const Real t0 = (dn == 0) ? sg : Real(0), t1 = (dn == 1) ? sg : Real(0), t2 = (dn == 2) ? sg : Real(0);
+      if constexpr (K == 8) {
 #pragma unroll
-      for (int v = 0; v < NV; ++v) Ls[rnd][v] = fma(t2, D[2][v], fma(t1, D[1][v], fma(t0, D[0][v], Q[v])));
+        for (int d = 0; d < 3; ++d)
+          if (dn == d) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) Ls[rnd][v] = fma(sg, D[d][v], Q[v]);
+          }
+      } else {
+        // the weights of the two other axes are zero, so their fused terms
+        // add exact zeros
+        const Real t0 = (dn == 0) ? sg : Real(0), t1 = (dn == 1) ? sg : Real(0), t2 = (dn == 2) ? sg : Real(0);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) Ls[rnd][v] = fma(t2, D[2][v], fma(t1, D[1][v], fma(t0, D[0][v], Q[v])));
+      }
       int nc = 0;
       floor_state<Real>(Ls[rnd], rfr, pfr, nc);
       pending |= Pend(nc) << (2 * (SITE_B + rnd));
@@ -898,10 +961,9 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
 #pragma unroll
         for (int v = 0; v < NV; ++v) FL[v * NFACE + f] = s[v];
       }
-    } else if (!((Lb[rnd] >> G::B_US) & EB(1))) {
-      const int f = int(Lb[rnd] >> G::B_FS);
+    } else if (const LayerCell lc = layer_of(rnd); !lc.up) {
 #pragma unroll
-      for (int v = 0; v < NV; ++v) FL[v * NFACE + f] = Ls[rnd][v];
+      for (int v = 0; v < NV; ++v) FL[v * NFACE + lc.face] = Ls[rnd][v];
     } else {
 #pragma unroll
       for (int v = 0; v < NV; ++v) FR[v * NUPPER + (i - NCORE)] = Ls[rnd][v];
@@ -930,8 +992,8 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
                                          Fc[r][2]);
       pending |= (Pend(nc[0]) << (2 * (SITE_R + 3 * r))) | (Pend(nc[1]) << (2 * (SITE_R + 3 * r + 1))) |
                  (Pend(nc[2]) << (2 * (SITE_R + 3 * r + 2)));
-    } else if ((Lb[rnd] >> G::B_US) & EB(1)) {
-      const int f = int(Lb[rnd] >> G::B_FS), dn = int((Lb[rnd] >> G::B_DS) & EB(3)), k = i - NCORE;
+    } else if (const LayerCell lc = layer_of(rnd); lc.up) {
+      const int f = lc.face, dn = lc.dn, k = i - NCORE;
       const int iu = 1 + dn, i1 = (dn == 0) ? 2 : 1, i2 = (dn == 2) ? 2 : 3;
       HllcSide<Real> side;
       hllc_n<Real>(FL[f], FL[iu * NFACE + f], FL[i1 * NFACE + f], FL[i2 * NFACE + f], FL[4 * NFACE + f], FR[k],
@@ -955,9 +1017,9 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
 #pragma unroll
         for (int v = 0; v < NV; ++v) SF[v * NFACE + f] = Fc[r][d][v];
       }
-    } else if ((Lb[rnd] >> G::B_US) & EB(1)) {
+    } else if (const LayerCell lc = layer_of(rnd); lc.up) {
       // Fl is in the face-normal frame: rotate back on the way out
-      const int f = int(Lb[rnd] >> G::B_FS), dn = int((Lb[rnd] >> G::B_DS) & EB(3));
+      const int f = lc.face, dn = lc.dn;
       const int iu = 1 + dn, i1 = (dn == 0) ? 2 : 1, i2 = (dn == 2) ? 2 : 3;
       SF[f] = Fl[rnd][0];
       SF[iu * NFACE + f] = Fl[rnd][1];
@@ -1147,8 +1209,8 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
       const int f = int(pending >> (2 * (SITE_A + rnd))) & 3;
       if (!f) continue;
       // a conversion: counted when the position is one of the tile's own leaf cells
-      const int raw = int(ST.a[tid + NT * rnd] >> G::A_RS);
-      const int sx = raw % G::R - 2, sy = (raw / G::R) % G::R - 2, sz = raw / (G::R * G::R) - 2;
+      int sx, sy, sz;
+      position_of<K>(ST.a[tid + NT * rnd], sx, sy, sz);
       if (census_own(hb, sx, sy, sz) && census_kind<K>(tab, ref, fl, hb, A.n_oct, sx, sy, sz) == 1) nfl += f;
     }
 #pragma unroll
@@ -1157,9 +1219,9 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
       if (!f) continue;
       // a one-layer face state: the face between the cell and the core, whose
       // lower cell is this cell (lower layer) or the core cell below it
-      const EB e = ST.b[tid + NT * rnd];
-      const int iw = int(e & LMASK), dn = int((e >> G::B_DS) & EB(3));
-      const bool up = (e >> G::B_US) & EB(1);
+      const LayerCell lc = layer_of(rnd);
+      const int iw = lc.iw, dn = lc.dn;
+      const bool up = lc.up;
       const int x = (iw % G::WB) - 1 - (up && dn == 0), y = (iw % G::WBB) / G::WB - 1 - (up && dn == 1),
                 z = iw / G::WBB - 1 - (up && dn == 2);
       if (census_face<K>(tab, ref, fl, hb, A.n_oct, x, y, z, dn)) nfl += f;
