@@ -147,8 +147,13 @@ ry_status fail(ry_ctx* c, ry_status s, const char* fmt, ...) {
 // per workgroup, the hardware dispatcher as the queue.
 constexpr ry_tuning kDefaultTuning{1, 0, 4, 1, 1, 4};
 
-// 4^3-cell tiles up to which one-level steps are chained (chained_steps).
-constexpr int32_t kChainSmallTiles = 8192;
+// 4^3-cell tiles up to which one-level steps are chained (chained_steps):
+// every tile of such a launch forms lambda again, against one finalize launch
+// a step.  FP64 periodic cubes, us a step chained / with the launch: 11.7 /
+// 14.3 (512 tiles), 27.7 / 29.9 (4096), 49.5 / 51.4 (10 648), 60.6 / 62.5
+// (13 824), 88.7 / 88.9 (21 952), 126.9 / 126.0 (32 768).  The 8^3-cell tiles
+// have an eighth of the tiles and are chained at every size.
+constexpr int32_t kChainSmallTiles = 16384;
 
 void* dalloc(ry_ctx* c, size_t bytes) {
   if (bytes == 0) bytes = 256;
