@@ -123,7 +123,7 @@ def settle(step, ms=None):
 
 
 def timed_reps(h, steps, reps=REPS):
-    """Wall time of `steps` coarse steps (graph replay, the production path),
+    """Wall time of `steps` coarse steps as a user runs them (`ry_advance`),
     `reps` times; returns (median seconds, all repetitions)."""
     import torch
     h.set_timing(False)
@@ -201,7 +201,7 @@ def pcie_inclusive(h, steps):
 
 def run_amr_pair(prob, tune, fixed, timed_steps, eager_steps=0, keep=False):
     """Both precision forms of one (AMR or uniform) workload: each advanced
-    its configuration's coarse steps (the first ones capture the graphs),
+    its configuration's coarse steps,
     compared, then timed (median of REPS repetitions of `timed_steps`)."""
     import torch
     res, hs = {}, {}
@@ -248,7 +248,7 @@ def run_amr_pair(prob, tune, fixed, timed_steps, eager_steps=0, keep=False):
 
 def run_zoom_only(precision, steps, warmup, tune, fixed, eager):
     """The zoom hierarchy alone (for profiling): `warmup` untimed coarse
-    steps, then `steps` timed ones, replayed from captured graphs or, with
+    steps, then `steps` timed ones, as `ry_advance` runs them or, with
     `eager`, launched one by one with HIP events around every kernel (the
     hydro kernels' summed time per coarse step then gives the hydro
     kernels' rate against HBM)."""
@@ -580,7 +580,7 @@ def main():
         return
     if args.only in ("batch", "batch-mixed"):
         # the 512 batched boxes alone (profiling): `warmup` untimed 20-step
-        # runs (graph capture), then one timed 20-step run
+        # runs, then one timed 20-step run
         from paper_2411_14631_amd import BatchHydro
         prec = "mixed" if args.only == "batch-mixed" else "fp64"
         boxes = W.batch(512)
@@ -653,7 +653,7 @@ def main():
         log(f"bench: uniform 128^3 {prec}")
         h, build_s = make(uprob, prec, tune, fixed)
         e0 = h.totals()[4]
-        h.advance(uprob.n_steps)                 # the configuration's 10 steps (captures the graphs)
+        h.advance(uprob.n_steps)                 # the configuration's 10 steps
         hs[prec] = (h, e0, h.floors())
     mixed_err = compare_forms(hs["fp64"][0], hs["mixed"][0], hs["fp64"][1], hs["mixed"][1])
     mixed_err["steps"] = uprob.n_steps
@@ -663,7 +663,7 @@ def main():
         cups = cell_updates_per_coarse_step(h)
         h.advance(args.warmup)
         settle(lambda: h.advance(8))
-        med, reps = timed_reps(h, args.steps)                 # value: graph replay, the production path
+        med, reps = timed_reps(h, args.steps)                 # value: the steps as a user runs them
         nl, ms = eager_kernel_time(h, args.steps)             # the kernel's own time (HIP events)
         res[prec] = dict(cups=cups, med=med, reps=reps, kernel_ms=ms / max(nl, 1), tuning=h.tuning(),
                          floors=hs[prec][2], pcie=pcie_inclusive(h, args.steps) if prec == "fp64" else None)
@@ -745,7 +745,7 @@ def main():
             log(f"bench: batch 512 boxes {prec}")
             bh = BatchHydro(boxes, prec)
             btune = bh.autotune()[0] if tune else bh.tuning()
-            bh.run(20)                                  # the workload's 20 steps (captures the graph)
+            bh.run(20)                                  # the workload's 20 steps
             bhs[prec] = bh
             batch[prec] = {"tuning": btune}
         batch["mixed"]["vs_fp64"] = compare_batches(bhs["fp64"], bhs["mixed"], boxes)
