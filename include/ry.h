@@ -154,7 +154,7 @@ ry_status ry_upload(ry_ctx* ctx, int32_t level, const double* U);
 ry_status ry_batch_create(const ry_config* cfgs, int32_t nbox, const double* const* U0, ry_ctx** out);
 /* nsteps steps of every box, each box with its own CFL dt computed on the
  * device, one hydro launch per step over the tiles of all boxes (with the
- * queue-fed tuning, and with 4^3-cell tiles past 8192 of them, a captured
+ * queue-fed tuning, and with 4^3-cell tiles past 16384 of them, a captured
  * graph of the steps, reused while nsteps and the state parity repeat).
  * Syncs. */
 ry_status ry_batch_run(ry_ctx* ctx, int32_t nsteps);
@@ -180,7 +180,11 @@ typedef struct {
 /* ry_set_tuning sets the tuning of every level; ry_get_tuning returns the
  * tuning of level_min.  RY_EINVAL for a combination without a kernel (see
  * the fields).  Choosing the 8^3-cell tile builds its tile tables on the
- * device (syncs). */
+ * device (syncs).  Until the first ry_set_tuning, ry_set_level_tuning or
+ * ry_autotune of a context, the tuning is {1, 0, 4, 1, 1, 4} on every level,
+ * and on a mesh of one level without passive scalars it stands for a launch
+ * chosen by the mesh's size (one wavefront per 4^3-cell tile, four, or the
+ * 8^3-cell tile); set, it means just what it says. */
 ry_status ry_set_tuning(ry_ctx* ctx, const ry_tuning* t);
 ry_status ry_get_tuning(const ry_ctx* ctx, ry_tuning* t);
 /* Tuning of one level (RY_EINVAL outside level_min..level_max).  Choosing

@@ -72,6 +72,7 @@ struct ry_ctx {
   int num_cu = 256;
   // launch tuning of the hydro kernel, per level (index level - level_min)
   ry_tuning tune[RY_MAX_LEVELS];
+  bool tuned = false;                     // by the caller (ry_set_tuning, ry_set_level_tuning, ry_autotune)
   // device scalars
   double* d_smax = nullptr;               // max signal speed per level / per box
   unsigned long long* d_slots = nullptr;  // per level: SMAX_SLOTS partial maxima of the fused CFL
@@ -407,12 +408,51 @@ ry_status enqueue_cfl_all(ry_ctx* c) {
   return RY_OK;
 }
 
+// The launches of a one-level mesh that the caller has not tuned, by its size
+// (FP64, us a step of chained steps: 1 / 2 / 4 wavefronts per 4^3-cell tile /
+// 8^3-cell tile):
+//     512 tiles (32^3)    11.7 / 10.9 / 10.0 / 12.4
+//     729 tiles (36^3)    12.7 / 11.5 / 10.8 / 12.7
+//   1,000 tiles (40^3)    13.9 / 12.7 / 14.6 / 13.1
+//   1,728 tiles (48^3)    16.8 / 18.0 / 19.8 / 13.8
+//   3,220 tiles (90x54x38) 24.3 / 24.8 / 29.7 / 18.1
+//   8,000 tiles (80^3)    40.4 / 45.0 / 60.7 / 29.9
+// Up to three tiles per CU the chip holds every wavefront at once with four
+// to a tile (three per SIMD), and a launch lasts as long as one tile's chain:
+// the chain is spread over four.  Above, the work counts, of which the
+// 8^3-cell tile does less per cell -- as long as its tiles are filled: at most
+// a third more cells in them (K = 8) than in the 4^3-cell ones, its advantage
+// on full tiles.
+constexpr ry_tuning kSmallTuning{1, 0, 4, 1, 4, 4}, kLargeTuning{1, 0, 4, 1, 8, 8};
+constexpr int32_t kSmallTilesPerCu = 3;
+
+// The untuned launch of the mesh (a level's own tuning where the rule does
+// not apply), before a look at whether the 8^3-cell tile's tables exist.
+const ry_tuning& default_tuning(const ry_ctx* c) {
+  const DevLevel& L = c->lev[0];
+  if (c->tuned || c->batch || c->nlev != 1 || c->cfg.nscalar != 0) return c->tune[0];
+  if (L.n_tile <= kSmallTilesPerCu * c->num_cu) return kSmallTuning;
+  int64_t v4 = 1, v8 = 1;
+  for (int a = 0; a < 3; ++a) {
+    const int64_t n = 2 * int64_t(c->dom.noct(c->cfg.level_min, a));
+    v4 *= (n + 3) / 4 * 4;
+    v8 *= (n + 7) / 8 * 8;
+  }
+  return 3 * v8 <= 4 * v4 ? kLargeTuning : c->tune[0];
+}
+const ry_tuning& launch_tuning(const ry_ctx* c, int k) {
+  if (c->tuned || c->nlev != 1) return c->tune[k];
+  const ry_tuning& t = default_tuning(c);
+  // without memory for the 8^3-cell tile's tables: the default launch
+  return t.tile_cells == 8 && !c->lev[0].super_ok ? c->tune[0] : t;
+}
+
 // Whether the context's steps are chained (Chain): one level, and a launch
 // whose workgroups' share of the time-step work costs less than the finalize
 // launch it replaces.
 bool chained_steps(const ry_ctx* c) {
   if (c->nlev != 1) return false;
-  const ry_tuning& t = c->tune[0];
+  const ry_tuning& t = launch_tuning(c, 0);
   if (t.persistent) return false;
   return t.tile_cells == 8 || c->lev[0].n_tile <= kChainSmallTiles;
 }
@@ -625,6 +665,15 @@ ry_status build_ghost_read(ry_ctx* c) {
 // Super-tile tables for every level whose tuning uses the 8^3-cell tile
 // (after a mesh change, or a tuning change).
 ry_status ensure_super(ry_ctx* c) {
+  if (!c->tuned && c->nlev == 1 && default_tuning(c).tile_cells == 8 && !c->lev[0].super_ok && c->lev[0].n_oct > 0) {
+    const std::string keep = c->err;
+    const ry_status s = build_super(c, 0);
+    if (s && s != RY_ENOMEM) return s;
+    if (s) {                              // the caller did not ask for them: go on without
+      free_super(c, c->lev[0]);
+      c->err = keep;
+    }
+  }
   for (int k = 0; k < c->nlev; ++k) {
     DevLevel& L = c->lev[k];
     if (c->tune[k].tile_cells == 8 && !L.super_ok && L.n_oct > 0) {
@@ -638,7 +687,7 @@ ry_status ensure_super(ry_ctx* c) {
 // One hydro launch of level k with the level's tuning (or `t`): on the small
 // tiles or, for the 8^3-cell tile, on the level's super-tiles.
 ry_status enqueue_hydro(ry_ctx* c, const HydroArgs& a, int k, const ry_tuning* t = nullptr) {
-  const ry_tuning& tu = t ? *t : c->tune[k];
+  const ry_tuning& tu = t ? *t : launch_tuning(c, k);
   HydroArgs b = a;
   if (tu.tile_cells == 8) {
     const DevLevel& L = c->lev[k];
@@ -1952,6 +2001,7 @@ ry_status ry_set_tuning(ry_ctx* c, const ry_tuning* t) {
   ry_status s = check_tuning(c, *t);
   if (s) return s;
   std::fill(std::begin(c->tune), std::end(c->tune), *t);
+  c->tuned = true;
   drop_all_graphs(c);
   if (c->built && (s = ensure_super(c))) return s;
   return RY_OK;
@@ -1972,6 +2022,7 @@ ry_status ry_set_level_tuning(ry_ctx* c, int32_t level, const ry_tuning* t) {
   ry_status s = check_tuning(c, *t);
   if (s) return s;
   c->tune[level - c->cfg.level_min] = *t;
+  c->tuned = true;
   drop_all_graphs(c);
   if (c->built && (s = ensure_super(c))) return s;
   return RY_OK;
@@ -2106,6 +2157,7 @@ ry_status ry_autotune(ry_ctx* c, ry_tuning* best, double* times_ms, int32_t max_
   if (times_ms)
     for (int i = 0; i < n && i < max_cand; ++i) times_ms[i] = coarse[i];
   std::copy(std::begin(chosen), std::end(chosen), c->tune);
+  c->tuned = true;
   drop_all_graphs(c);
   // tables of levels left without the 8^3-cell tile are not needed any more
   for (int k = 0; k < c->nlev; ++k)

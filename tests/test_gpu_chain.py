@@ -61,9 +61,10 @@ def same(a, b):
         np.testing.assert_array_equal(x, y)
 
 
-@pytest.mark.parametrize("n,bc", [(8, W.BC_PERIODIC), (30, W.BC_OUTFLOW), (84, W.BC_PERIODIC)])
+@pytest.mark.parametrize("n,bc", [(8, W.BC_PERIODIC), (30, W.BC_OUTFLOW), (84, W.BC_PERIODIC),
+                                  (104, W.BC_PERIODIC)])
 def test_chained_steps_equal_unchained(ry, n, bc):
-    # 84^3: 9261 4^3-cell tiles, past the chained range
+    # 104^3: 17,576 4^3-cell tiles, past the chained range
     prob = dataclasses.replace(W.random_smooth(n, seed=5, mach=0.9), bc=(bc,) * 6)
     ref = run(ry, prob, QUEUE)
     for t in (K4, K8, K84):
