@@ -182,8 +182,8 @@ typedef struct {
  * the fields).  Choosing the 8^3-cell tile builds its tile tables on the
  * device (syncs).  Until the first ry_set_tuning, ry_set_level_tuning or
  * ry_autotune of a context, the tuning is {1, 0, 4, 1, 1, 4} on every level,
- * and on a mesh of one level without passive scalars it stands for a launch
- * chosen by the mesh's size (one wavefront per 4^3-cell tile, four, or the
+ * and on a mesh of one level without passive scalars, and in a batch, it
+ * stands for a launch chosen by the number of cells (one wavefront per 4^3-cell tile, four, or the
  * 8^3-cell tile); set, it means just what it says. */
 ry_status ry_set_tuning(ry_ctx* ctx, const ry_tuning* t);
 ry_status ry_get_tuning(const ry_ctx* ctx, ry_tuning* t);

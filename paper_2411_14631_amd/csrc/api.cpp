@@ -72,6 +72,7 @@ struct ry_ctx {
   int num_cu = 256;
   // launch tuning of the hydro kernel, per level (index level - level_min)
   ry_tuning tune[RY_MAX_LEVELS];
+  int64_t pad4 = 0, pad8 = 0;             // cells the base level's (a batch's boxes') 4^3- and 8^3-cell tiles hold
   bool tuned = false;                     // by the caller (ry_set_tuning, ry_set_level_tuning, ry_autotune)
   // device scalars
   double* d_smax = nullptr;               // max signal speed per level / per box
@@ -153,8 +154,11 @@ constexpr ry_tuning kDefaultTuning{1, 0, 4, 1, 1, 4};
 // a step.  FP64 periodic cubes, us a step chained / with the launch: 11.7 /
 // 14.3 (512 tiles), 27.7 / 29.9 (4096), 49.5 / 51.4 (10 648), 60.6 / 62.5
 // (13 824), 88.7 / 88.9 (21 952), 126.9 / 126.0 (32 768).  The 8^3-cell tiles
-// have an eighth of the tiles and are chained at every size.
-constexpr int32_t kChainSmallTiles = 16384;
+// have an eighth of the tiles and are chained at every size.  The mixed
+// form's tiles are shorter and meet on one box's 64 slots: 10.7 / 12.9 (512),
+// 20.9 / 21.5 (4096), 28.3 / 25.8 (5832), 48.9 / 42.2 (13 824); a batch has 64
+// for each box (16 boxes, 4461 tiles 20.5 / 22.4; 32 boxes, 5454 22.3 / 24.4).
+constexpr int32_t kChainSmallTiles = 16384, kChainSmallTilesMixed = 4096;
 
 void* dalloc(ry_ctx* c, size_t bytes) {
   if (bytes == 0) bytes = 256;
@@ -408,7 +412,8 @@ ry_status enqueue_cfl_all(ry_ctx* c) {
   return RY_OK;
 }
 
-// The launches of a one-level mesh that the caller has not tuned, by its size
+// The launches of a one-level mesh, or a batch, that the caller has not tuned,
+// by its size
 // (FP64, us a step of chained steps: 1 / 2 / 4 wavefronts per 4^3-cell tile /
 // 8^3-cell tile):
 //     512 tiles (32^3)    11.7 / 10.9 / 10.0 / 12.4
@@ -422,7 +427,12 @@ ry_status enqueue_cfl_all(ry_ctx* c) {
 // the chain is spread over four.  Above, the work counts, of which the
 // 8^3-cell tile does less per cell -- as long as its tiles are filled: at most
 // a third more cells in them (K = 8) than in the 4^3-cell ones, its advantage
-// on full tiles.
+// on full tiles (FP64 128^3 126 / 92.8).  The mixed form's advantage is that
+// only while its launches are short (4^3- / 8^3-cell tiles: 42^3, 1.30 times
+// the cells: 13.5 / 11.7; 128 x 128 x 12, 1.33: 18.1 / 14.8), a fifth further
+// on (128 x 128 x 20, 5120 tiles, 1.20: 23.6 / 20.2; 92^3, 12,167, 1.14: 38.9 /
+// 35.9) and an eighth in the end (128^3 79.7 / 71.2; 64 boxes of 16 to 32
+// cells, 17,839, 1.21: 50.0 / 51.3).
 constexpr ry_tuning kSmallTuning{1, 0, 4, 1, 4, 4}, kLargeTuning{1, 0, 4, 1, 8, 8};
 constexpr int32_t kSmallTilesPerCu = 3;
 
@@ -430,15 +440,21 @@ constexpr int32_t kSmallTilesPerCu = 3;
 // not apply), before a look at whether the 8^3-cell tile's tables exist.
 const ry_tuning& default_tuning(const ry_ctx* c) {
   const DevLevel& L = c->lev[0];
-  if (c->tuned || c->batch || c->nlev != 1 || c->cfg.nscalar != 0) return c->tune[0];
+  if (c->tuned || c->nlev != 1 || c->cfg.nscalar != 0) return c->tune[0];
   if (L.n_tile <= kSmallTilesPerCu * c->num_cu) return kSmallTuning;
+  const bool mixed = c->cfg.precision == RY_MIXED;
+  const int64_t den = !mixed || L.n_tile <= 4096 ? 3 : L.n_tile <= 16384 ? 5 : 8;
+  return den * c->pad8 <= (den + 1) * c->pad4 ? kLargeTuning : c->tune[0];
+}
+// Adds one box's cells in whole tiles (pad4, pad8).
+void add_padded(ry_ctx* c, const ry_config& cfg) {
   int64_t v4 = 1, v8 = 1;
   for (int a = 0; a < 3; ++a) {
-    const int64_t n = 2 * int64_t(c->dom.noct(c->cfg.level_min, a));
-    v4 *= (n + 3) / 4 * 4;
-    v8 *= (n + 7) / 8 * 8;
+    v4 *= (int64_t(cfg.nbase[a]) + 3) / 4 * 4;
+    v8 *= (int64_t(cfg.nbase[a]) + 7) / 8 * 8;
   }
-  return 3 * v8 <= 4 * v4 ? kLargeTuning : c->tune[0];
+  c->pad4 += v4;
+  c->pad8 += v8;
 }
 const ry_tuning& launch_tuning(const ry_ctx* c, int k) {
   if (c->tuned || c->nlev != 1) return c->tune[k];
@@ -454,7 +470,8 @@ bool chained_steps(const ry_ctx* c) {
   if (c->nlev != 1) return false;
   const ry_tuning& t = launch_tuning(c, 0);
   if (t.persistent) return false;
-  return t.tile_cells == 8 || c->lev[0].n_tile <= kChainSmallTiles;
+  return t.tile_cells == 8 ||
+         c->lev[0].n_tile <= (c->cfg.precision == RY_MIXED && !c->batch ? kChainSmallTilesMixed : kChainSmallTiles);
 }
 
 // Start of a chained run: the slots and records of phase 0.
@@ -865,6 +882,7 @@ ry_status ry_create(const ry_config* cfg, ry_ctx** out) {
   c->cfg = *cfg;
   c->dom = make_dom(*cfg);
   c->nlev = cfg->level_max - cfg->level_min + 1;
+  add_padded(c, *cfg);
   std::fill(std::begin(c->tune), std::end(c->tune), kDefaultTuning);
   if ((s = init_common(c))) {
     delete c;
@@ -1794,6 +1812,7 @@ ry_status ry_batch_create(const ry_config* cfgs, int32_t nbox, const double* con
       oc.push_back(H[0].oz[o]);
     }
     for (int a = 0; a < 3; ++a) box_noct.push_back(cfgs[b].nbase[a] / 2);
+    add_padded(c, cfgs[b]);
     Ubox[b] = H[0].U;
     off += t.n_oct;
   }
@@ -1838,6 +1857,10 @@ ry_status ry_batch_create(const ry_config* cfgs, int32_t nbox, const double* con
   if (hipStreamSynchronize(c->stream) != hipSuccess) {
     ry_destroy(c);
     return RY_EHIP;
+  }
+  if ((s = ensure_super(c))) {
+    ry_destroy(c);
+    return s;
   }
   c->built = true;
   *out = c;

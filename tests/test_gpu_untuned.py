@@ -1,4 +1,4 @@
-"""The launch an untuned one-level mesh takes by its size, against the default
+"""The launch an untuned one-level mesh or batch takes by its size, against the default
 4^3-cell tile set explicitly: the same states, times and floor counts (results
 do not depend on the tuning, so the tolerance is 0), the reported tuning the
 default either way.  Sizes either side of the lines: up to 768 tiles, above
@@ -57,6 +57,8 @@ def run(h, lvl):
     ((90, 54, 38), W.BC_OUTFLOW),
     ((96, 64, 10), W.BC_PERIODIC),       # 8^3-cell tiles a third emptier
     ((160, 96, 4), W.BC_PERIODIC),       # half empty: not taken
+    ((84, 60, 76), W.BC_PERIODIC),       # 5,985
+    ((132, 132, 20), W.BC_PERIODIC),     # 5,445: the mixed form's 8^3-cell tiles too empty
 ])
 def test_untuned_equals_default_tuning(ry, dims, bc, precision):
     prob = box(dims, bc)
@@ -66,6 +68,26 @@ def test_untuned_equals_default_tuning(ry, dims, bc, precision):
     b = run(h, prob.level_min)
     assert a[0] and a[-1]
     for x, y in zip(a, b):
+        np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("sides", [(6, 16, 18), (16, 32, 40, 24), (18, 18, 34, 34), (48, 6, 2, 22)])
+def test_untuned_batch_equals_default_tuning(ry, sides, precision):
+    # 4^3-cell tiles: 197; 1,792 (8^3-cell tiles full); 1,708 (8^3-cell tiles too empty); 1,953
+    boxes = [box((s, s, s), W.BC_PERIODIC) for s in sides]
+    res = []
+    for tune in (False, True):
+        h = ry.BatchHydro(boxes, precision)
+        if tune:
+            h.set_tuning(**DEFAULT)
+        assert h.tuning() == DEFAULT
+        for n in (1, 4, 3):
+            h.run(n)
+        res.append([h.download(b) for b in range(len(boxes))] + [h.box_info(b)[1] for b in range(len(boxes))])
+        assert h.tuning() == DEFAULT
+        h.close()
+    for x, y in zip(*res):
         np.testing.assert_array_equal(x, y)
 
 
