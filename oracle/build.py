@@ -1,6 +1,6 @@
 """Compile the oracle (plain C, FP64, no FMA contraction, OpenMP static).
 
-Test infrastructure only: the checker is built here, never used by the
+Test infrastructure only: the oracle is built here, never used by the
 product path.
 """
 import os
