@@ -26,11 +26,13 @@ struct Staging {
   hipEvent_t ev[kThreads] = {};
 
   // rows of `bytes` each, `stride` apart on the device, one after the other
-  // on the host; waits for the stream
+  // on the host; waits for the stream.  A per-thread stream's handle names
+  // another stream in every thread: only the caller's is behind the caller's
+  // work, so it takes the runtime's path.
   hipError_t download(void* host, const void* dev, size_t bytes, size_t stride, int rows, hipStream_t st) {
     const size_t total = bytes * size_t(rows);
     int device = 0;
-    if (total < kLeast || hipGetDevice(&device) != hipSuccess || !ready()) {
+    if (total < kLeast || st == hipStreamPerThread || hipGetDevice(&device) != hipSuccess || !ready()) {
       for (int r = 0; r < rows; ++r) {
         const hipError_t e = hipMemcpyAsync(static_cast<char*>(host) + r * bytes,
                                             static_cast<const char*>(dev) + r * stride, bytes,

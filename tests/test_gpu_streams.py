@@ -1,0 +1,63 @@
+"""Contexts on the calling thread's own stream (hipStreamPerThread): the same
+results bit for bit as on an ordinary stream, downloads of every size behind
+the work enqueued before them.
+"""
+import types
+
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+PER_THREAD = 2          # hipStreamPerThread's handle
+
+
+@pytest.fixture(scope="module")
+def ry():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2411_14631_amd import ry as R
+    R.lib()
+    return R
+
+
+def on_stream(ry, monkeypatch, make, per_thread):
+    import torch
+    with monkeypatch.context() as m:
+        if per_thread:
+            m.setattr(torch.cuda, "Stream", lambda device=None: types.SimpleNamespace(cuda_stream=PER_THREAD))
+        return make()
+
+
+@pytest.mark.parametrize("n", [24, 64])      # downloads of 0.5 MB and 10.5 MB
+def test_hydro_step_then_download(ry, monkeypatch, n):
+    prob = W.random_smooth(n, seed=3, mach=0.9)
+    out = []
+    for per_thread in (False, True):
+        h = on_stream(ry, monkeypatch, lambda: ry.Hydro(prob, torch_memory=False), per_thread)
+        dt = h.cfl_dt()
+        res = []
+        for _ in range(3):
+            h.hydro_step(prob.level_min, 0.5 * dt)      # asynchronous
+            res.append(h.download(prob.level_min))
+        h.close()
+        out.append(res)
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("shape", [(20, 24, 36), (110, 110, 112)])    # both forms of the solver
+def test_poisson_vectors(ry, monkeypatch, shape):
+    b = np.random.default_rng(4).standard_normal(shape)
+    b -= b.mean()
+    out = []
+    for per_thread in (False, True):
+        g = on_stream(ry, monkeypatch, lambda: ry.Poisson(shape, torch_memory=False), per_thread)
+        g.set_rhs(b)
+        g.iterate(5)
+        out.append([g.download(v) for v in ry.POISSON_VECTORS])
+        g.close()
+    for x, y in zip(*out):
+        np.testing.assert_array_equal(x, y)
