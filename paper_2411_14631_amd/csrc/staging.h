@@ -13,7 +13,6 @@
 #include <atomic>
 #include <cstddef>
 #include <cstring>
-#include <system_error>
 #include <thread>
 
 namespace ry {
@@ -64,7 +63,7 @@ struct Staging {
     for (int w = 0; w < nextra; ++w) {
       try {
         extra[w] = std::thread(work, w + 1);
-      } catch (const std::system_error&) {
+      } catch (...) {                                    // no thread, or no host memory for one
         break;                                           // the threads there are do the work
       }
     }
