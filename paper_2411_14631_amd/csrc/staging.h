@@ -27,11 +27,14 @@ struct Staging {
   // rows of `bytes` each, `stride` apart on the device, one after the other
   // on the host; waits for the stream.  A per-thread stream's handle names
   // another stream in every thread: only the caller's is behind the caller's
-  // work, so it takes the runtime's path.
+  // work, so it takes the runtime's path.  So does memory the runtime knows
+  // (pinned or registered): the copy engine writes it in place (84 MB 1.5 ms
+  // against 2.7 through the chunks).
   hipError_t download(void* host, const void* dev, size_t bytes, size_t stride, int rows, hipStream_t st) {
     const size_t total = bytes * size_t(rows);
     int device = 0;
-    if (total < kLeast || st == hipStreamPerThread || hipGetDevice(&device) != hipSuccess || !ready()) {
+    if (total < kLeast || st == hipStreamPerThread || !pageable(host) || hipGetDevice(&device) != hipSuccess ||
+        !ready()) {
       for (int r = 0; r < rows; ++r) {
         const hipError_t e = hipMemcpyAsync(static_cast<char*>(host) + r * bytes,
                                             static_cast<const char*>(dev) + r * stride, bytes,
@@ -85,6 +88,12 @@ struct Staging {
   }
 
  private:
+  static bool pageable(const void* host) {
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, host) == hipSuccess) return a.type == hipMemoryTypeUnregistered;
+    (void)hipGetLastError();   // memory the runtime does not know: some versions report it as an error
+    return true;
+  }
   // the pinned chunks, on first use; without them copies take the runtime's path
   bool ready() {
     if (buf) return true;

@@ -1,6 +1,6 @@
 """Contexts on the calling thread's own stream (hipStreamPerThread): the same
 results bit for bit as on an ordinary stream, downloads of every size behind
-the work enqueued before them.
+the work enqueued before them.  Downloads into pinned and ordinary memory.
 """
 import types
 
@@ -61,3 +61,16 @@ def test_poisson_vectors(ry, monkeypatch, shape):
         g.close()
     for x, y in zip(*out):
         np.testing.assert_array_equal(x, y)
+
+
+def test_download_into_pinned_memory(ry):
+    import torch
+    prob = W.random_smooth(64, seed=3, mach=0.9)
+    h = ry.Hydro(prob)
+    h.advance(2)
+    ref = h.download(prob.level_min)
+    for off in (0, 1):                        # the allocation's first byte, and inside it
+        t = torch.full((ref.size + off,), -1.0, dtype=torch.float64, pin_memory=True)
+        assert ry.lib().ry_download(h.ctx, prob.level_min, t.data_ptr() + 8 * off) == ry.RY_OK
+        np.testing.assert_array_equal(t.numpy()[off:].reshape(ref.shape), ref)
+    h.close()

@@ -25,6 +25,7 @@ def program(tmp_path_factory):
     "pageable",             # chunks by several threads
     "per_thread_stream",    # the handle means the caller's stream in the caller's thread only
     "no_host_memory",       # threads that cannot be made: the caller does the work
+    "pinned",               # a destination the copy engine writes in place: one copy a row
 ])
 def test_staged_download(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True, timeout=60)
