@@ -160,6 +160,8 @@ constexpr ry_tuning kDefaultTuning{1, 0, 4, 1, 1, 4};
 // for each box (16 boxes, 4461 tiles 20.5 / 22.4; 32 boxes, 5454 22.3 / 24.4).
 constexpr int32_t kChainSmallTiles = 16384, kChainSmallTilesMixed = 4096;
 
+// nullptr when refused; the runtime's record of a refused hipMalloc (here or
+// in the hook) is cleared, which the next launch's check would report else.
 void* dalloc(ry_ctx* c, size_t bytes) {
   if (bytes == 0) bytes = 256;
   void* p = nullptr;
@@ -169,6 +171,7 @@ void* dalloc(ry_ctx* c, size_t bytes) {
     p = nullptr;
   }
   if (p) c->allocs.push_back(p);
+  else (void)hipGetLastError();
   return p;
 }
 
@@ -287,6 +290,7 @@ ry_status init_common(ry_ctx* c) {
 ry_status ensure_readback(ry_ctx* c) {
   if (!c->h_rb && hipHostMalloc(reinterpret_cast<void**>(&c->h_rb), sizeof(Readback)) != hipSuccess) {
     c->h_rb = nullptr;
+    (void)hipGetLastError();
     return fail(c, RY_ENOMEM, "pinned readback buffer");
   }
   return RY_OK;

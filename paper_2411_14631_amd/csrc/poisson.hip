@@ -794,6 +794,7 @@ void* palloc(ry_poisson* p, size_t bytes) {
   if (p->cfg.dev_alloc) a = p->cfg.dev_alloc(bytes, p->cfg.alloc_user);
   else if (hipMalloc(&a, bytes) != hipSuccess) a = nullptr;
   if (a) p->allocs.push_back(a);
+  else (void)hipGetLastError();   // a refused hipMalloc's, which the next launch's check would report
   return a;
 }
 
@@ -986,6 +987,7 @@ ry_status ry_poisson_create(const ry_poisson_config* cfg, ry_poisson** out) {
   ok = ok && (p->sc = static_cast<Scalars*>(palloc(p, sizeof(Scalars)))) != nullptr;
   if (ok && hipHostMalloc((void**)&p->h_done, sizeof(int32_t)) != hipSuccess) {
     p->h_done = nullptr;
+    (void)hipGetLastError();
     ok = false;
   }
   if (!ok) {
