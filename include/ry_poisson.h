@@ -14,9 +14,10 @@
  * the pipelined form of plain CG (M^-1 = I).  A periodic problem is
  * singular: b must have zero sum for the iteration to converge.  The
  * iterates, scalars and vectors below are the method's for every size;
- * problems of at least 5 * 2^18 cells are iterated in a form that keeps x, r
- * and p only and applies M^-1 and A where the recurrences would carry u, w,
- * s, q and z (equal in exact arithmetic, half the memory traffic).
+ * problems of at least 5 * 2^18 cells that are not thin (about 10 cells in x
+ * and y, 4 in z) are iterated in a form that keeps x, r and p only and
+ * applies M^-1 and A where the recurrences would carry u, w, s, q and z
+ * (equal in exact arithmetic, half the memory traffic).
  *
  * Conventions: every function returns a ry_status (include/ry.h); host
  * pointers are borrowed for the duration of the call; device memory belongs
@@ -53,7 +54,8 @@ typedef struct {
 typedef struct ry_poisson ry_poisson;
 
 /* Allocates nine FP64 grid vectors (x, r, u, w twice, z, q, s, p; from
- * 5 * 2^18 cells on five: x, r twice, p twice) plus reduction scratch and an eps history of RY_POISSON_HIST entries.
+ * 5 * 2^18 cells on, where not thin, five: x, r twice, p twice) plus reduction
+ * scratch and an eps history of RY_POISSON_HIST entries.
  * RY_EINVAL: bad sizes or enums; RY_ENOMEM: allocation failed (nothing
  * leaks); RY_EHIP: no device. */
 #define RY_POISSON_HIST 65536

@@ -1,10 +1,10 @@
 // Uniform-level Poisson solver on gfx950: the preconditioned conjugate-
 // gradient iterates of PPCG (Ghysels & Vanroose 2014, Algorithm 4) with the
 // seven-point preconditioner 13/12 (centre), 1/6 (face neighbours), in one of
-// two forms chosen by the problem's size (kTwoSweepCells):
+// two forms chosen by the problem's size and shape (plan_sweeps):
 //
 // Pipelined form (small problems: each launch counts, the vectors sit in the
-// caches).  One launch per iteration i: every workgroup sums the partials of
+// caches; and thin grids).  One launch per iteration i: every workgroup sums the partials of
 // gamma_i = r_i.u_i and delta_i = w_i.u_i that the launch before left, in
 // one fixed order, and forms alpha_i and beta_i itself; then a z-marching
 // stencil sweep forms m_i = M^-1 w_i and n_i = A m_i from w_i staged in LDS,
@@ -35,6 +35,7 @@
 // Loads run two planes ahead of their use.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -70,11 +71,29 @@ constexpr int NVEC = 9;                                  // pipelined: x r u w0 
 // pipelined / 28.2 two-sweep, 101 x 99 x 103 29.0 / 32.7, 128^3 44.4 / 39.6,
 // 160^3 105 / 60).
 constexpr int64_t kTwoSweepCells = int64_t(5) << 18;
+// They also have to be thick enough along z (a sweep loads four planes beside
+// its chunk's own, and works on two of them) and to fill the larger tile (us
+// per iteration, pipelined / two-sweep; n2 x n1 x n0): 1 x 2048^2 131 / 276, 3 x 1024^2 84 / 100,
+// 4 x 1024^2 111 / 110, 6 x 1024^2 165 / 130; 30,000 x 8 x 8 (an eighth of the
+// tile) 74 / 130, 10,000 x 12 x 12 (0.28) 53 / 60, 20,000 x 16 x 16 (a half) 147 / 107.
+constexpr int kTwoSweepPlanes = 4;
+constexpr double kTwoSweepFill = 1.0 / 3;
 // Workgroups per sweep at most (z chunks are added up to it).  Large: two per
 // CU, all resident, no second round.  Small: each workgroup pays the scalar
 // step and four halo planes, so few, thicker chunks (64^3: 11.3 us per
-// iteration with 512, 15.5 with 1024, 11.8 with 256).
-constexpr int kTargetSmall = 512, kTargetLarge = 512;
+// iteration with 512, 15.5 with 1024, 11.8 with 256) -- up to kLongChunk
+// planes, past which the chain of planes counts: twice as many then, and as
+// many as fit a CU (six) where hardly a lane has a cell (512 / 1024 / 1536
+// workgroups: 30,000 x 8 x 8 83 / 74 / 91 us, 81,920 x 4 x 4 179 / 137 / 129,
+// 1,310,720 x 1 x 1 2384 / 1736 / 1322).
+constexpr int kTargetSmall = 512, kTargetLong = 1024, kTargetThin = 1536, kTargetLarge = 512;
+constexpr int kLongChunk = 16;
+constexpr double kThinFill = 1.0 / 8;
+// Every workgroup of a sweep sums all partials itself, up to this many of
+// them; past it a launch of 2.5 us leaves kSums of them for the sweeps to read
+// (us per iteration without / with: 1000 x 1000 (2016 workgroups) 49 / 41,
+// 16,384 x 128 (4096) 122 / 76, 1 x 4096^2 (32,768) 3106 / 480).
+constexpr int kMaxPartials = 1024, kSums = 256;
 
 struct Grid {
   int32_t n0, n1, n2, bc;
@@ -106,7 +125,9 @@ struct IterArgs {
   double *x, *r, *u, *z, *q, *s, *p;
   Scalars* sc;
   double* hist;
-  double* part;   // two sets (by parity) of [2][gridDim.x]
+  double* part;   // written: two sets (by parity) of [2][gridDim.x]
+  double* sum;    // read: two sets of [2][nsum] (part itself, or its sums by reduce_kernel)
+  int32_t nsum;
   int32_t cz;     // z planes per workgroup
   int32_t par;    // parity of the iteration index
 };
@@ -116,7 +137,9 @@ struct CgArgs {
   double *x, *r[2], *p[2];
   Scalars* sc;
   double* hist;
-  double *part_g, *part_d;   // [gridDim.x] each
+  double *part_g, *part_d;   // written: [gridDim.x] each
+  double *sum_g, *sum_d;     // read: [nsum] each (as IterArgs::sum)
+  int32_t nsum;
   int32_t cz;
 };
 
@@ -315,13 +338,27 @@ __device__ __forceinline__ double six(const double* pl, int c, double below, dou
 // 22.3, was 34.7).  One thread per cell and two rounds over the halo points:
 // a thread per halo point costs more wavefronts, whose prologue is what
 // counts here (48 x 40 x 36 9.9 us).
+//
+// MANY: more workgroups than the chip holds at once (thin grids).  Their
+// throughput counts instead: six to a CU instead of four, the recurrence
+// vectors streamed past the caches, one sum per thread to read.
 // ---------------------------------------------------------------------------
-template <int PC>
-__global__ __launch_bounds__(NTH) void ppcg_iterate_kernel(IterArgs A) {
+template <bool MANY>
+__device__ __forceinline__ double stream_load(const double* p) {
+  if constexpr (MANY) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool MANY>
+__device__ __forceinline__ void stream_store(double v, double* p) {
+  if constexpr (MANY) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+template <int PC, bool MANY>
+__global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(MANY ? 6 : 4))) void ppcg_iterate_kernel(IterArgs A) {
   constexpr int TX = SmallTile::TX, TY = SmallTile::TY;
   constexpr int WX = TX + 4, WPL = WX * (TY + 4), NW = (WPL + NTH - 1) / NTH;   // planes with a 2-cell halo
   constexpr int MX = TX + 2, MPL = MX * (TY + 2), NM = (MPL + NTH - 1) / NTH;   // and a 1-cell halo
-  static_assert(TX * TY == NTH, "one thread per cell");
+  static_assert(TX * TY == NTH && kSums == NTH, "one thread per cell, and per sum");
   __shared__ double Wp[5][WPL], Mp[3][MPL];
   __shared__ double red[2][NTH / 64];
   Scalars* sc = A.sc;
@@ -329,7 +366,7 @@ __global__ __launch_bounds__(NTH) void ppcg_iterate_kernel(IterArgs A) {
   const Chunk<SmallTile> C(g, A.cz);
   const int tid = threadIdx.x, tx = tid % TX, ty = tid / TX;
   const int nb = gridDim.x;
-  const double* part_in = A.part + int64_t(A.par) * 2 * nb;
+  const double* sum_in = A.sum + int64_t(A.par) * 2 * A.nsum;
   double* part_out = A.part + int64_t(A.par ^ 1) * 2 * nb;
   const double* __restrict__ win = A.w[A.par];
   double* __restrict__ wout = A.w[A.par ^ 1];
@@ -363,14 +400,24 @@ __global__ __launch_bounds__(NTH) void ppcg_iterate_kernel(IterArgs A) {
   };
   auto load_rec = [&](int z) {
     const int64_t i = col + C.plane * z;
-    return Rec{A.z[i], A.q[i], A.s[i], A.p[i], A.u[i], A.x[i], A.r[i]};
+    return Rec{stream_load<MANY>(A.z + i), stream_load<MANY>(A.q + i), stream_load<MANY>(A.s + i),
+               stream_load<MANY>(A.p + i), stream_load<MANY>(A.u + i), stream_load<MANY>(A.x + i),
+               stream_load<MANY>(A.r + i)};
   };
   // the first plane's five w planes and recurrences, and the partials
   double wr[5][NW];
 #pragma unroll
   for (int k = 0; k < 5; ++k) load_w(C.z0 - 2 + k, wr[k]);
-  Rec rec = load_rec(C.z0), nxt{};
-  double gd[2] = {strided_sum(part_in, nb), strided_sum(part_in + nb, nb)};
+  Rec rec{}, nxt{};
+  if constexpr (!MANY) rec = load_rec(C.z0);
+  double gd[2];
+  if constexpr (MANY) {
+    gd[0] = sum_in[tid];
+    gd[1] = sum_in[kSums + tid];
+  } else {
+    gd[0] = strided_sum(sum_in, A.nsum);
+    gd[1] = strided_sum(sum_in + A.nsum, A.nsum);
+  }
   // looked at with the loads under way
   const Scalars::Step st = sc->step[A.par];
   if (st.done) {
@@ -436,8 +483,9 @@ __global__ __launch_bounds__(NTH) void ppcg_iterate_kernel(IterArgs A) {
     const bool more = z + 1 < C.z1;
     if (more) {
       load_w(z + 3, wr[0]);
-      nxt = load_rec(z + 1);
+      if constexpr (!MANY) nxt = load_rec(z + 1);
     }
+    if constexpr (MANY) rec = load_rec(z);
     if (own) {
       const int64_t i = col + C.plane * z;
       const double* m0 = Mp[mslot(z)];
@@ -452,14 +500,14 @@ __global__ __launch_bounds__(NTH) void ppcg_iterate_kernel(IterArgs A) {
       const double rr = rec.r - alpha * ss;
       const double uu = rec.u - alpha * qq;
       const double ww = wv - alpha * zz;
-      A.z[i] = zz;
-      A.q[i] = qq;
-      A.s[i] = ss;
-      A.p[i] = pp;
-      A.x[i] = rec.x + alpha * pp;
-      A.r[i] = rr;
-      A.u[i] = uu;
-      wout[i] = ww;
+      stream_store<MANY>(zz, A.z + i);
+      stream_store<MANY>(qq, A.q + i);
+      stream_store<MANY>(ss, A.s + i);
+      stream_store<MANY>(pp, A.p + i);
+      stream_store<MANY>(rec.x + alpha * pp, A.x + i);
+      stream_store<MANY>(rr, A.r + i);
+      stream_store<MANY>(uu, A.u + i);
+      stream_store<MANY>(ww, wout + i);
       acc[0] += rr * uu;
       acc[1] += ww * uu;
     }
@@ -468,7 +516,7 @@ __global__ __launch_bounds__(NTH) void ppcg_iterate_kernel(IterArgs A) {
       __syncthreads();
       comp_m(z + 2);
       __syncthreads();
-      rec = nxt;
+      if constexpr (!MANY) rec = nxt;
     }
   }
   block_sum(acc, red);   // the barrier after comp_m separates it from the first sum
@@ -506,7 +554,7 @@ __global__ __launch_bounds__(LargeTile::NT) void cg_direction_kernel(CgArgs A) {
   __shared__ double s_beta;
   __shared__ int s_stop;
   if (threadIdx.x < 64) {
-    const double gamma = wave_total(A.part_g, gridDim.x);
+    const double gamma = wave_total(A.sum_g, A.nsum);
     double eps;
     const bool stop = stop_at(sc, st.iter, gamma, eps);
     if (threadIdx.x == 0) {
@@ -578,7 +626,7 @@ __global__ __launch_bounds__(LargeTile::NT) void cg_update_kernel(CgArgs A) {
   Pp[0][P.c] = p0;
   __shared__ double s_alpha;
   if (threadIdx.x < 64) {
-    const double a = dir.gamma / wave_total(A.part_d, gridDim.x);
+    const double a = dir.gamma / wave_total(A.sum_d, A.nsum);
     if (threadIdx.x == 0) {
       s_alpha = a;
       if (blockIdx.x == 0) sc->step[0] = {a, dir.gamma, dir.iter + 1, 0};
@@ -619,6 +667,19 @@ __global__ __launch_bounds__(LargeTile::NT) void cg_update_kernel(CgArgs A) {
   }
   block_sum(acc, red);
   if (threadIdx.x == 0) A.part_g[blockIdx.x] = acc[0];
+}
+
+// Sums of contiguous shares of n partials, one per workgroup (gridDim.y
+// quantities), in a fixed order.  Also launched behind iterations that no
+// longer run: the same partials then give the same sums again.
+__global__ __launch_bounds__(NTH) void reduce_kernel(const double* __restrict__ part, int n,
+                                                     double* __restrict__ sum) {
+  __shared__ double red[1][NTH / 64];
+  const int64_t b = blockIdx.x, m = gridDim.x;
+  const int first = int(b * n / m), last = int((b + 1) * n / m);
+  double a[1] = {strided_sum(part + int64_t(blockIdx.y) * n + first, last - first)};
+  block_sum(a, red);
+  if (threadIdx.x == 0) sum[blockIdx.y * m + b] = a[0];
 }
 
 // (Re)arm the stopping rule: absolute max_iter, or relative to the current
@@ -754,10 +815,11 @@ struct ry_poisson {
   bool two_sweep = false;
   double* v[NVEC] = {};        // x r u w0 w1 z q s p; two-sweep: x r0 r1 p0 p1
   double* part = nullptr;      // pipelined: [2][2][nblk]; two-sweep: [2][nblk] (gamma, p.Ap)
+  double* sum = nullptr;       // part, or as part with nsum for nblk
   double* hist = nullptr;
   Scalars* sc = nullptr;
   int32_t* h_done = nullptr;   // pinned
-  int nblk = 0, cz = 0;
+  int nblk = 0, nsum = 0, cz = 0;
   ry::Staging staging;         // pinned buffers of the downloads
   bool ready = false;          // set_rhs done
   int64_t iter = 0;            // the device's iteration index (once the stream's work is done)
@@ -834,6 +896,8 @@ IterArgs iter_args(ry_poisson* p, int par) {
   a.sc = p->sc;
   a.hist = p->hist;
   a.part = p->part;
+  a.sum = p->sum;
+  a.nsum = p->nsum;
   a.cz = p->cz;
   a.par = par;
   return a;
@@ -851,8 +915,45 @@ CgArgs cg_args(ry_poisson* p) {
   a.hist = p->hist;
   a.part_g = p->part;
   a.part_d = p->part + p->nblk;
+  a.sum_g = p->sum;
+  a.sum_d = p->sum + p->nsum;
+  a.nsum = p->nsum;
   a.cz = p->cz;
   return a;
+}
+
+// The sums the sweeps read, from nq quantities' partials starting at set k
+// (of nblk values each).
+void launch_reduce(ry_poisson* p, int k, int nq) {
+  if (p->nsum == p->nblk) return;
+  hipLaunchKernelGGL(reduce_kernel, dim3(p->nsum, nq), dim3(NTH), 0, p->stream, p->part + int64_t(k) * p->nblk,
+                     p->nblk, p->sum + int64_t(k) * p->nsum);
+}
+
+// The solver's form and its sweeps' workgroups (the constants at the top say
+// where the lines lie).
+void plan_sweeps(ry_poisson* p) {
+  const Grid& g = p->g;
+  int64_t cols = 0;
+  double fill = 0.0;
+  auto tiles = [&](int tx, int ty) {
+    cols = int64_t((g.n0 + tx - 1) / tx) * ((g.n1 + ty - 1) / ty);
+    fill = double(g.n0) * g.n1 / (double(cols) * tx * ty);
+  };
+  auto chunks = [&](int target) {
+    const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(target / cols, g.n2));
+    p->cz = int32_t((g.n2 + nch - 1) / nch);
+    p->nblk = int(cols * ((g.n2 + p->cz - 1) / p->cz));
+  };
+  tiles(LargeTile::TX, LargeTile::TY);
+  chunks(kTargetLarge);
+  p->two_sweep = p->N >= kTwoSweepCells && p->cz >= kTwoSweepPlanes && fill >= kTwoSweepFill;
+  if (!p->two_sweep) {
+    tiles(SmallTile::TX, SmallTile::TY);
+    chunks(kTargetSmall);
+    if (p->cz > kLongChunk) chunks(fill < kThinFill ? kTargetThin : kTargetLong);
+  }
+  p->nsum = p->nblk > kMaxPartials ? kSums : p->nblk;
 }
 
 // The slot of Scalars::step that the next iteration reads.
@@ -874,17 +975,20 @@ ry_status launch_iteration(ry_poisson* p, int par, bool timed) {
   const bool pc = p->cfg.precond == RY_PC_STENCIL7;
   if (p->two_sweep) {
     const CgArgs a = cg_args(p);
-    if (pc) {
-      hipLaunchKernelGGL(cg_direction_kernel<RY_PC_STENCIL7>, grid, block, 0, p->stream, a);
-      hipLaunchKernelGGL(cg_update_kernel<RY_PC_STENCIL7>, grid, block, 0, p->stream, a);
-    } else {
-      hipLaunchKernelGGL(cg_direction_kernel<RY_PC_NONE>, grid, block, 0, p->stream, a);
-      hipLaunchKernelGGL(cg_update_kernel<RY_PC_NONE>, grid, block, 0, p->stream, a);
-    }
+    if (pc) hipLaunchKernelGGL(cg_direction_kernel<RY_PC_STENCIL7>, grid, block, 0, p->stream, a);
+    else hipLaunchKernelGGL(cg_direction_kernel<RY_PC_NONE>, grid, block, 0, p->stream, a);
+    launch_reduce(p, 1, 1);
+    if (pc) hipLaunchKernelGGL(cg_update_kernel<RY_PC_STENCIL7>, grid, block, 0, p->stream, a);
+    else hipLaunchKernelGGL(cg_update_kernel<RY_PC_NONE>, grid, block, 0, p->stream, a);
+    launch_reduce(p, 0, 1);
   } else {
     const IterArgs a = iter_args(p, par);
-    if (pc) hipLaunchKernelGGL(ppcg_iterate_kernel<RY_PC_STENCIL7>, grid, block, 0, p->stream, a);
-    else hipLaunchKernelGGL(ppcg_iterate_kernel<RY_PC_NONE>, grid, block, 0, p->stream, a);
+    const bool many = p->nsum != p->nblk;
+    if (pc && many) hipLaunchKernelGGL((ppcg_iterate_kernel<RY_PC_STENCIL7, true>), grid, block, 0, p->stream, a);
+    else if (pc) hipLaunchKernelGGL((ppcg_iterate_kernel<RY_PC_STENCIL7, false>), grid, block, 0, p->stream, a);
+    else if (many) hipLaunchKernelGGL((ppcg_iterate_kernel<RY_PC_NONE, true>), grid, block, 0, p->stream, a);
+    else hipLaunchKernelGGL((ppcg_iterate_kernel<RY_PC_NONE, false>), grid, block, 0, p->stream, a);
+    launch_reduce(p, 2 * (par ^ 1), 2);
   }
   if (timed) PCHK(p, hipEventRecord(p->ev.back().second, p->stream));
   PCHK(p, hipGetLastError());
@@ -970,19 +1074,12 @@ ry_status ry_poisson_create(const ry_poisson_config* cfg, ry_poisson** out) {
     }
     p->own_stream = true;
   }
-  // z chunks: enough workgroups to fill 256 CUs several times over
-  p->two_sweep = N >= kTwoSweepCells;
-  const int tx = p->two_sweep ? LargeTile::TX : SmallTile::TX, ty = p->two_sweep ? LargeTile::TY : SmallTile::TY;
-  const int gx = (cfg->n[0] + tx - 1) / tx, gy = (cfg->n[1] + ty - 1) / ty;
-  int64_t nch = (p->two_sweep ? kTargetLarge : kTargetSmall) / (int64_t(gx) * gy);
-  if (nch > cfg->n[2]) nch = cfg->n[2];
-  if (nch < 1) nch = 1;
-  p->cz = int32_t((cfg->n[2] + nch - 1) / nch);
-  nch = (cfg->n[2] + p->cz - 1) / p->cz;
-  p->nblk = int(gx * gy * nch);
+  plan_sweeps(p);
   bool ok = true;
   for (int k = 0; k < (p->two_sweep ? 5 : NVEC) && ok; ++k) ok = (p->v[k] = static_cast<double*>(palloc(p, sizeof(double) * N))) != nullptr;
   ok = ok && (p->part = static_cast<double*>(palloc(p, sizeof(double) * 4 * p->nblk))) != nullptr;
+  p->sum = p->part;
+  if (ok && p->nsum != p->nblk) ok = (p->sum = static_cast<double*>(palloc(p, sizeof(double) * 4 * p->nsum))) != nullptr;
   ok = ok && (p->hist = static_cast<double*>(palloc(p, sizeof(double) * RY_POISSON_HIST))) != nullptr;
   ok = ok && (p->sc = static_cast<Scalars*>(palloc(p, sizeof(Scalars)))) != nullptr;
   if (ok && hipHostMalloc((void**)&p->h_done, sizeof(int32_t)) != hipSuccess) {
@@ -1037,6 +1134,7 @@ ry_status ry_poisson_set_rhs(ry_poisson* p, const double* b, const double* x0) {
     hipLaunchKernelGGL(minv_kernel, dim3(blocks), dim3(256), 0, p->stream, p->g, p->cfg.precond, r, u);
     hipLaunchKernelGGL(apply_a_dots_kernel, dim3(p->nblk), dim3(NTH), 0, p->stream, p->g, r, u, w0, p->part);
   }
+  launch_reduce(p, 0, p->two_sweep ? 1 : 2);
   hipLaunchKernelGGL(ppcg_reset_kernel, dim3(1), dim3(1), 0, p->stream, p->sc);
   PCHK(p, hipGetLastError());
   p->ready = true;
