@@ -107,9 +107,10 @@ ry_status ry_hydro_step(ry_ctx* ctx, int32_t level, double dt);
 /* Up to n_coarse coarse steps, each with dt from the CFL rule clipped to
  * reach t_end exactly; dt stays on the device (no host sync per step).  A
  * step of one level is one launch (except with the queue-fed tuning, and with
- * 4^3-cell tiles past 16384 of them, mixed form 4096); other steps are
- * replayed from captured hipGraphs once a call length comes by a second time
- * on the same mesh and tuning.  *t_io: time in/out.  Syncs. */
+ * 4^3-cell tiles past 16384 of them, mixed form 4096); other steps go out in
+ * groups of 16, 8, 4, 2 and 1, each replayed from a captured hipGraph from its
+ * second use on the same mesh and tuning on (a call of 40 steps uses 16
+ * twice), whatever t_end is.  *t_io: time in/out.  Syncs. */
 ry_status ry_advance(ry_ctx* ctx, int32_t n_coarse, double t_end, double* t_io);
 
 /* Regrid between coarse steps (dynamic refinement, the refine_fine step of

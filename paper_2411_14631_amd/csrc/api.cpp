@@ -82,7 +82,7 @@ struct ry_ctx {
   std::vector<int64_t> seg_off;           // host copy
   int64_t part_cap = 0;                   // values d_part holds
   double* d_lam = nullptr;                // 1 / per box
-  double* d_t = nullptr;                  // 1 / per box
+  double* d_t = nullptr;                  // the time, and the t_end of the call / per box
   int32_t* d_flags = nullptr;             // [0]=skip [1]=done [2]=nstep [3]=err
   // the flags, the time, the levels' maximum signal speeds and the totals as
   // the stream's last work left them: written into pinned host memory by one
@@ -108,7 +108,6 @@ struct ry_ctx {
   // [parity of the base level buffer]
   hipGraphExec_t graph[5][2] = {};
   std::vector<int> graph_par[5][2];
-  double graph_tend[5][2] = {};
   bool graph_asked[5][2] = {};            // a run of that length has come by since the graphs were dropped
   // batch
   int nbox = 0;
@@ -305,7 +304,7 @@ ry_status alloc_scalars(ry_ctx* c, int nslot) {
   c->part_cap = npart;
   c->d_segoff = static_cast<int64_t*>(dalloc(c, sizeof(int64_t) * c->seg_off.size()));
   c->d_lam = static_cast<double*>(dalloc(c, sizeof(double) * nslot));
-  c->d_t = static_cast<double*>(dalloc(c, sizeof(double) * nslot));
+  c->d_t = static_cast<double*>(dalloc(c, sizeof(double) * (nslot + 1)));
   c->d_flags = static_cast<int32_t*>(dalloc(c, sizeof(int32_t) * 8));
   c->d_floors = static_cast<unsigned long long*>(dalloc(c, sizeof(unsigned long long)));
   c->d_queue = static_cast<unsigned int*>(dalloc(c, sizeof(unsigned int) * 8 * QUEUE_STRIDE));
@@ -779,7 +778,6 @@ ry_status enqueue_coarse_step(ry_ctx* c, double t_end, int phase) {
   f.nslot = c->nlev;
   f.cfl = c->cfg.cfl;
   for (int k = 0; k < c->nlev; ++k) f.dx[k] = level_dx(c, c->cfg.level_min + k);
-  f.t_end = t_end;
   f.t = c->d_t;
   f.lam = c->d_lam;
   f.skip = skip_ptr(c);
@@ -1631,7 +1629,6 @@ static ry_status capture_step(ry_ctx* c, int gi, int par, double t_end) {
   hipGraphDestroy(g);
   if (e != hipSuccess) return fail(c, RY_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
   c->graph_par[gi][par] = saved;
-  c->graph_tend[gi][par] = t_end;
   return RY_OK;
 }
 
@@ -1648,7 +1645,7 @@ ry_status ry_advance(ry_ctx* c, int32_t n_coarse, double t_end, double* t_io) {
     if ((s = chain_begin(c, *t_io))) return s;
   } else {
     if (!c->slots_valid && (s = enqueue_cfl_all(c))) return s;
-    if (launch_begin(*t_io, c->d_t, c->d_flags, c->stream)) return fail(c, RY_EHIP, "begin kernel");
+    if (launch_begin(*t_io, t_end, c->d_t, c->d_flags, c->stream)) return fail(c, RY_EHIP, "begin kernel");
   }
   // a chained step is one launch: enqueued directly it costs the host about
   // 2.5 us while the step runs, a graph launch 8 us before it does (32^3, two
@@ -1667,7 +1664,7 @@ ry_status ry_advance(ry_ctx* c, int32_t n_coarse, double t_end, double* t_io) {
       while ((1 << gi) > n_coarse - i) --gi;
       std::vector<int> now;
       for (auto& L : c->lev) now.push_back(L.cur);
-      const bool have = c->graph[gi][par] && c->graph_par[gi][par] == now && c->graph_tend[gi][par] == t_end;
+      const bool have = c->graph[gi][par] && c->graph_par[gi][par] == now;
       if (!have && !c->graph_asked[gi][par]) {
         // the first time on this mesh and tuning: launched one by one, which
         // costs less than capturing a graph that may never be used again

@@ -394,11 +394,11 @@ __device__ bool finalize_dt(const FinalizeArgs& A) {
     const double cand = ldexp(dtl, k);
     if (cand < best) best = cand;
   }
-  const double t = *A.t;
+  const double t = A.t[0], t_end = A.t[1];
   double dt = best;
   int last = 0;
-  if (dt >= A.t_end - t) {
-    dt = A.t_end - t;
+  if (dt >= t_end - t) {
+    dt = t_end - t;
     last = 1;
   }
   if (!(dt > 0.0)) {
@@ -408,7 +408,7 @@ __device__ bool finalize_dt(const FinalizeArgs& A) {
     return false;
   }
   *A.lam = dt / A.dx[0];
-  *A.t = last ? A.t_end : t + dt;
+  A.t[0] = last ? t_end : t + dt;
   *A.skip = 0;
   *A.nstep += 1;
   if (last) *A.done = 1;
@@ -461,8 +461,9 @@ int launch_finalize(const FinalizeArgs& a, void* stream) {
 // Bound: latency.  Kernel arguments and stores to pinned memory replace the
 // copy engine's path: a host-to-device and two device-to-host copies took
 // about 4 us each on the stream (32^3 box, two steps per call: 53.9 -> 49.1 us).
-__global__ void begin_kernel(double t, double* d_t, int32_t* flags) {
-  *d_t = t;
+__global__ void begin_kernel(double t, double t_end, double* d_t, int32_t* flags) {
+  d_t[0] = t;
+  d_t[1] = t_end;
   flags[0] = flags[1] = flags[2] = 0;
 }
 // slots: the end of a chained run of one box at `phase` as well
@@ -521,8 +522,8 @@ int launch_chain_end(unsigned long long* slots, const StepRec* rec, int nbox, in
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_begin(double t, double* d_t, int32_t* flags, void* stream) {
-  hipLaunchKernelGGL(begin_kernel, dim3(1), dim3(1), 0, (hipStream_t)stream, t, d_t, flags);
+int launch_begin(double t, double t_end, double* d_t, int32_t* flags, void* stream) {
+  hipLaunchKernelGGL(begin_kernel, dim3(1), dim3(1), 0, (hipStream_t)stream, t, t_end, d_t, flags);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 int launch_readback(int32_t* flags, double* t, const double* smax, int nsmax, const double* tot,

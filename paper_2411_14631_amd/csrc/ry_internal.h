@@ -269,8 +269,7 @@ struct FinalizeArgs {
   double cfl;
   double dx[RY_MAX_LEVELS];        // AMR: dx of each level; batch: unused
   const double* dx_box;            // batch: dx per box
-  double t_end;
-  double* t;                       // AMR: 1 value; batch: per box
+  double* t;                       // AMR: the time and t_end; batch: per box
   double* lam;                     // AMR: 1 value; batch: per box
   int32_t* skip;
   int32_t* done;
@@ -304,8 +303,8 @@ int launch_chain_begin(unsigned long long* slots, StepRec* rec, int nbox, const 
 // box 0's step count in *nstep.
 int launch_chain_end(unsigned long long* slots, const StepRec* rec, int nbox, int phase, double* t_dev, int32_t* nstep,
                      void* stream);
-// Start of a run of coarse steps: the time, and flags 0-2 (skip, done, steps) cleared.
-int launch_begin(double t, double* d_t, int32_t* flags, void* stream);
+// Start of a run of coarse steps: the time and t_end, and flags 0-2 (skip, done, steps) cleared.
+int launch_begin(double t, double t_end, double* d_t, int32_t* flags, void* stream);
 int launch_zero_u32(unsigned int* p, int64_t n, void* stream);
 int launch_zero_u64(unsigned long long* p, int64_t n, void* stream);
 int launch_totals(const double* U, int64_t plane, int64_t n_oct, const uint8_t* refined, double vol, int nv,
