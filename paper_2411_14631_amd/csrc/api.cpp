@@ -95,6 +95,7 @@ struct ry_ctx {
   double* d_tot = nullptr;
   double* d_dx_box = nullptr;
   int64_t* d_box_noct = nullptr;          // batch: octs per axis of each box (3 per box)
+  int32_t* d_box_bc = nullptr;            // batch: boundaries of each box (6 per box)
   bool slots_valid = false;
   // one-level contexts: the chained steps' slots and records ([4][boxes])
   unsigned long long* d_cslots = nullptr;
@@ -618,6 +619,7 @@ ry_status build_super(ry_ctx* c, int k) {
     if (c->batch) {
       D.tile_box = L.tile_box;
       D.box_noct = c->d_box_noct;
+      D.box_bc = c->d_box_bc;
     }
     if (launch_super_keys(L.tab, nt, L.doc, L.n_oct, D, skey, ssub, start, c->stream) ||
         launch_scan(start, excl, nt, stmp, c->h_rb->rg.total, c->stream) ||
@@ -1780,6 +1782,7 @@ ry_status ry_batch_create(const ry_config* cfgs, int32_t nbox, const double* con
   std::vector<int32_t> oct_box;
   std::vector<int32_t> oc;                  // oct coordinates in each box, x y z interleaved
   std::vector<int64_t> box_noct;            // octs per axis of each box
+  std::vector<int32_t> box_bc;               // boundaries of each box
   std::vector<std::vector<double>> Ubox(nbox);
   int64_t off = 0;
   for (int b = 0; b < nbox; ++b) {
@@ -1813,6 +1816,7 @@ ry_status ry_batch_create(const ry_config* cfgs, int32_t nbox, const double* con
       oc.push_back(H[0].oz[o]);
     }
     for (int a = 0; a < 3; ++a) box_noct.push_back(cfgs[b].nbase[a] / 2);
+    box_bc.insert(box_bc.end(), cfgs[b].bc, cfgs[b].bc + 6);
     add_padded(c, cfgs[b]);
     Ubox[b] = H[0].U;
     off += t.n_oct;
@@ -1850,6 +1854,7 @@ ry_status ry_batch_create(const ry_config* cfgs, int32_t nbox, const double* con
     D.doc = upload_vec(c, oc, ok);
     c->d_dx_box = upload_vec(c, c->box_dx, ok);
     c->d_box_noct = upload_vec(c, box_noct, ok);
+    c->d_box_bc = upload_vec(c, box_bc, ok);
   }
   if (!ok || alloc_scalars(c, nbox)) {
     ry_destroy(c);

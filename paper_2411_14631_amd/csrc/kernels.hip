@@ -762,8 +762,10 @@ __global__ void super_table_kernel(const int32_t* __restrict__ tab, const int32_
     for (int a = 0; a < 3; ++a) {
       o[a] *= 4;
       const int64_t n = D.box_noct ? D.box_noct[3 * int64_t(box) + a] : D.noct[a];
-      if (o[a] == 0 && D.bc[2 * a] == RY_BC_OUTFLOW) fl |= (1u << (2 * a));
-      if (o[a] + 4 >= n && D.bc[2 * a + 1] == RY_BC_OUTFLOW) fl |= (2u << (2 * a));
+      const int32_t lo = D.box_bc ? D.box_bc[6 * int64_t(box) + 2 * a] : D.bc[2 * a];
+      const int32_t hi = D.box_bc ? D.box_bc[6 * int64_t(box) + 2 * a + 1] : D.bc[2 * a + 1];
+      if (o[a] == 0 && lo == RY_BC_OUTFLOW) fl |= (1u << (2 * a));
+      if (o[a] + 4 >= n && hi == RY_BC_OUTFLOW) fl |= (2u << (2 * a));
       const int64_t past = o[a] + 4 - n;
       cut[a] = past > 0 ? int(2 * past) : 0;
     }

@@ -315,10 +315,12 @@ int launch_copy(const double* src, double* dst, int64_t n, void* stream);
 struct SuperDom {
   int64_t noct[3];                   // octs per axis of the level
   int32_t bc[6];
-  // batched boxes: the box of every small tile and the octs per axis of
-  // every box (3 per box); nullptr for a level of one domain
+  // batched boxes: the box of every small tile, the octs per axis (3 per box)
+  // and the boundaries (6 per box) of every box; nullptr for a level of one
+  // domain
   const int32_t* tile_box;
   const int64_t* box_noct;
+  const int32_t* box_bc;
 };
 int super_table_slots();             // 6^3 oct neighbourhood entries per super-tile
 // per small tile: its block key, its position in the block, block starts
