@@ -492,12 +492,19 @@ __device__ __forceinline__ void core_face_flux(const Real* FL, int f, const Real
 }
 
 // Time step of a box from its largest signal speed (the arithmetic of the
-// finalize kernel for one level); returns lambda = dt / dx, 0 when the step
-// does not run.
+// finalize kernel for one level, or for a batch); returns lambda = dt / dx, 0
+// when the step does not run.  A batch's boxes all take every step, also one
+// whose dt underflows to 0: they share the buffers' parity.
 __device__ __forceinline__ double chain_step(const StepRec& in, double smax, double cfl, double dx, double t_end,
-                                             StepRec& out) {
+                                             bool batch, StepRec& out) {
 #pragma clang fp contract(off)
   out = in;
+  if (batch) {
+    const double dt = cfl * dx / smax;
+    out.t = in.t + dt;
+    out.nstep = in.nstep + 1;
+    return dt / dx;
+  }
   if (in.done) return 0.0;
   double dt = INFINITY;
   if (smax > 0.0) dt = cfl * dx / smax;
@@ -832,7 +839,7 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
     const StepRec in = C.rec_in[box];
     StepRec out;
     const double l = chain_step(in, wave_max(__longlong_as_double(static_cast<long long>(sv))), C.cfl,
-                                C.dx_box ? C.dx_box[box] : C.dx, C.t_end, out);
+                                C.dx_box ? C.dx_box[box] : C.dx, C.t_end, C.dx_box != nullptr, out);
     const bool runs = out.nstep != in.nstep;
     if (lane == 0) {
       S.lam = l;
