@@ -440,16 +440,17 @@ ry_status enqueue_cfl_all(ry_ctx* c) {
 constexpr ry_tuning kSmallTuning{1, 0, 4, 1, 4, 4}, kLargeTuning{1, 0, 4, 1, 8, 8};
 constexpr int32_t kSmallTilesPerCu = 3;
 
-// The untuned launch of the mesh (a level's own tuning where the rule does
-// not apply), before a look at whether the 8^3-cell tile's tables exist.
-const ry_tuning& default_tuning(const ry_ctx* c) {
+// The base level's launch when the caller tunes nothing, before a look at
+// whether the 8^3-cell tile's tables exist.
+const ry_tuning& untuned_launch(const ry_ctx* c) {
   const DevLevel& L = c->lev[0];
-  if (c->tuned || c->nlev != 1 || c->cfg.nscalar != 0) return c->tune[0];
+  if (c->nlev != 1 || c->cfg.nscalar != 0) return kDefaultTuning;
   if (L.n_tile <= kSmallTilesPerCu * c->num_cu) return kSmallTuning;
   const bool mixed = c->cfg.precision == RY_MIXED;
   const int64_t den = !mixed || L.n_tile <= 4096 ? 3 : L.n_tile <= 16384 ? 5 : 8;
-  return den * c->pad8 <= (den + 1) * c->pad4 ? kLargeTuning : c->tune[0];
+  return den * c->pad8 <= (den + 1) * c->pad4 ? kLargeTuning : kDefaultTuning;
 }
+const ry_tuning& default_tuning(const ry_ctx* c) { return c->tuned ? c->tune[0] : untuned_launch(c); }
 // Adds one box's cells in whole tiles (pad4, pad8).
 void add_padded(ry_ctx* c, const ry_config& cfg) {
   int64_t v4 = 1, v8 = 1;
@@ -470,13 +471,12 @@ const ry_tuning& launch_tuning(const ry_ctx* c, int k) {
 // Whether the context's steps are chained (Chain): one level, and a launch
 // whose workgroups' share of the time-step work costs less than the finalize
 // launch it replaces.
-bool chained_steps(const ry_ctx* c) {
-  if (c->nlev != 1) return false;
-  const ry_tuning& t = launch_tuning(c, 0);
-  if (t.persistent) return false;
+bool chained_under(const ry_ctx* c, const ry_tuning& t) {
+  if (c->nlev != 1 || t.persistent) return false;
   return t.tile_cells == 8 ||
          c->lev[0].n_tile <= (c->cfg.precision == RY_MIXED && !c->batch ? kChainSmallTilesMixed : kChainSmallTiles);
 }
+bool chained_steps(const ry_ctx* c) { return c->nlev == 1 && chained_under(c, launch_tuning(c, 0)); }
 
 // Start of a chained run: the slots and records of phase 0.
 ry_status chain_begin(ry_ctx* c, double t) {
@@ -2066,8 +2066,54 @@ ry_status ry_get_level_tuning(const ry_ctx* c, int32_t level, ry_tuning* t) {
   RY_ABI_CATCH
 }
 
-// Time level k's hydro launch under tuning t (four launches, the best of the
-// last three), writing only the level's other state buffer.
+static double* probe_clock(ry_ctx* c) {   // phase 3's slots, which a chained run clears before it fills them
+  return reinterpret_cast<double*>(c->d_cslots + int64_t(3) * (c->batch ? c->nbox : 1) * CHAIN_SLOTS);
+}
+// One step of a one-level context as it runs under tuning t: the chained
+// launch, or the time-step launches and the hydro launch.  Writes the level's
+// other state buffer; times, flags and errors go to scratch memory, the
+// maxima's buffers are left changed.
+static ry_status enqueue_probe_step(ry_ctx* c, const ry_tuning& t) {
+  const int nbox = c->batch ? c->nbox : 1;
+  double* const clock = probe_clock(c);
+  auto* const flags = reinterpret_cast<int32_t*>(c->d_partial);
+  HydroArgs a = hydro_args(c, c->cfg.level_min, 0);
+  a.floors = nullptr;
+  a.err = flags + 3;
+  if (chained_under(c, t)) {
+    set_chain(c, a, 0, INFINITY);
+    return enqueue_hydro(c, a, 0, &t);
+  }
+  FinalizeArgs f{};
+  f.slots = c->d_slots;
+  f.smax = c->d_smax;
+  f.nslot = nbox;
+  f.cfl = c->cfg.cfl;
+  f.dx[0] = level_dx(c, c->cfg.level_min);
+  f.dx_box = c->d_dx_box;
+  f.t = clock;
+  f.lam = c->d_lam;
+  f.skip = flags;
+  f.done = flags + 1;
+  f.nstep = flags + 2;
+  f.batch = c->batch ? 1 : 0;
+  if (c->batch) {
+    if (ry_status s = enqueue_seg_max(c)) return s;
+    a.tile_smax = c->d_part;
+  } else {
+    a.skip = f.skip;
+    a.smax_bits = c->d_slots;
+  }
+  if (launch_finalize(f, c->stream)) return fail(c, RY_EHIP, "finalize kernel");
+  a.lam_dev = c->d_lam;
+  return enqueue_hydro(c, a, 0, &t);
+}
+
+// Time level k's hydro launch under tuning t, in a one-level context a step
+// of kProbeSteps in a row (a small box's step is as long as the gap that an
+// event leaves in front of the first); four times, the best of the last
+// three.  Writes only the level's other state buffer.
+constexpr int kProbeSteps = 4;
 static ry_status time_level(ry_ctx* c, int k, const ry_tuning& t, double* ms_out) {
   hipEvent_t a, b;
   hipEventCreateWithFlags(&a, hipEventDisableSystemFence);
@@ -2076,7 +2122,6 @@ static ry_status time_level(ry_ctx* c, int k, const ry_tuning& t, double* ms_out
   ry_status s = RY_OK;
   const int l = c->cfg.level_min + k;
   HydroArgs h = hydro_args(c, l, 0);
-  h.lam_dev = c->batch ? c->d_lam : nullptr;
   h.lam_host = 0.1;
   h.record_reg = 0;
   h.reg_own = nullptr;
@@ -2086,12 +2131,13 @@ static ry_status time_level(ry_ctx* c, int k, const ry_tuning& t, double* ms_out
   h.skip = nullptr;
   for (int rep = 0; rep < 4 && !s; ++rep) {
     hipEventRecord(a, c->stream);
-    s = enqueue_hydro(c, h, k, &t);
+    const int n = c->nlev == 1 ? kProbeSteps : 1;
+    for (int j = 0; j < n && !s; ++j) s = c->nlev == 1 ? enqueue_probe_step(c, t) : enqueue_hydro(c, h, k, &t);
     hipEventRecord(b, c->stream);
     hipEventSynchronize(b);
     float ms = 0.f;
     hipEventElapsedTime(&ms, a, b);
-    if (rep > 0) best = std::min(best, double(ms));
+    if (rep > 0) best = std::min(best, double(ms) / n);
   }
   hipEventDestroy(a);
   hipEventDestroy(b);
@@ -2102,10 +2148,16 @@ static ry_status time_level(ry_ctx* c, int k, const ry_tuning& t, double* ms_out
 ry_status ry_autotune(ry_ctx* c, ry_tuning* best, double* times_ms, int32_t max_cand, int32_t* n_cand) {
   RY_ABI_TRY
   if (!c || !c->built) return RY_EINVAL;
-  if (c->batch) {
-    // the batched launch reads per-box lambda: make sure it holds values
+  if (c->nlev == 1) {
+    // the timed steps are whole ones: every kind finds the state's maxima
+    // where it reads them, and a clock without an end
     ry_status s0 = enqueue_cfl_all(c);
+    if (!s0) s0 = chain_begin(c, 0.0);
     if (s0) return s0;
+    if (!c->batch &&
+        launch_begin(0.0, INFINITY, probe_clock(c), reinterpret_cast<int32_t*>(c->d_partial), c->stream))
+      return fail(c, RY_EHIP, "begin kernel");
+    c->slots_valid = c->smax_valid = c->chain_valid = false;
   }
   std::vector<ry_tuning> cand;
   for (int wpt : {1, 2, 4})
@@ -2137,9 +2189,9 @@ ry_status ry_autotune(ry_ctx* c, ry_tuning* best, double* times_ms, int32_t max_
     if (s) return s;
   }
   // per level: stage 1 times every candidate once (best of three launches);
-  // stage 2 times the three fastest and the default launch again in six
+  // stage 2 times the three fastest and the untuned launch again in six
   // interleaved rounds (drift and noise hit all alike); the median decides,
-  // and a candidate must beat the default by more than 2% to replace it
+  // and a candidate must beat the untuned launch by more than 2% to replace it
   // (isolated launches and the production sequence differ by a few percent)
   std::vector<double> coarse(n, 0.0);   // per candidate: the coarse step's hydro time if used on every level
   ry_tuning chosen[RY_MAX_LEVELS];
@@ -2159,9 +2211,9 @@ ry_status ry_autotune(ry_ctx* c, ry_tuning* best, double* times_ms, int32_t max_
     for (int i = 0; i < n && i < 3; ++i) fin.push_back(cand[order[i]]);
     int idef = -1;
     for (size_t i = 0; i < fin.size(); ++i)
-      if (same_tuning(fin[i], kDefaultTuning)) idef = int(i);
-    if (idef < 0 && hydro_tuning_supported(c->cfg.precision, c->cfg.nscalar, kDefaultTuning)) {
-      fin.push_back(kDefaultTuning);
+      if (same_tuning(fin[i], untuned_launch(c))) idef = int(i);
+    if (idef < 0 && hydro_tuning_supported(c->cfg.precision, c->cfg.nscalar, untuned_launch(c))) {
+      fin.push_back(untuned_launch(c));
       idef = int(fin.size()) - 1;
     }
     std::vector<std::vector<double>> t2(fin.size());
