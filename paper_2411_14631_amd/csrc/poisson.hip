@@ -1125,6 +1125,8 @@ ry_status ry_poisson_set_rhs(ry_poisson* p, const double* b, const double* x0) {
     for (int k = 0; k < 4; ++k) clear.v[k] = p->v[5 + k];
   PCHK(p, hipMemcpyAsync(stage, b, bytes, hipMemcpyHostToDevice, p->stream));
   if (x0) PCHK(p, hipMemcpyAsync(x, x0, bytes, hipMemcpyHostToDevice, p->stream));
+  // b and x0 are the caller's again when this returns
+  if (!ry::Staging::pageable(b) || (x0 && !ry::Staging::pageable(x0))) PCHK(p, hipStreamSynchronize(p->stream));
   const int blocks = int(std::min<int64_t>((p->N + 255) / 256, 8192));
   hipLaunchKernelGGL(residual_kernel, dim3(blocks), dim3(256), 0, p->stream, p->g, stage, x, x0 ? 0 : 1, r, clear);
   if (p->two_sweep) {

@@ -24,6 +24,15 @@ struct Staging {
   char* buf = nullptr;                                  // a chunk per thread, kept for the owner's life
   hipEvent_t ev[kThreads] = {};
 
+  // memory the runtime does not know: its copies are done when they return,
+  // those of other host memory only behind the stream
+  static bool pageable(const void* host) {
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, host) == hipSuccess) return a.type == hipMemoryTypeUnregistered;
+    (void)hipGetLastError();   // memory the runtime does not know: some versions report it as an error
+    return true;
+  }
+
   // rows of `bytes` each, `stride` apart on the device, one after the other
   // on the host; waits for the stream.  A per-thread stream's handle names
   // another stream in every thread: only the caller's is behind the caller's
@@ -88,12 +97,6 @@ struct Staging {
   }
 
  private:
-  static bool pageable(const void* host) {
-    hipPointerAttribute_t a{};
-    if (hipPointerGetAttributes(&a, host) == hipSuccess) return a.type == hipMemoryTypeUnregistered;
-    (void)hipGetLastError();   // memory the runtime does not know: some versions report it as an error
-    return true;
-  }
   // the pinned chunks, on first use; without them copies take the runtime's path
   bool ready() {
     if (buf) return true;

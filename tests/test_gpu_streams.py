@@ -74,3 +74,27 @@ def test_download_into_pinned_memory(ry):
         assert ry.lib().ry_download(h.ctx, prob.level_min, t.data_ptr() + 8 * off) == ry.RY_OK
         np.testing.assert_array_equal(t.numpy()[off:].reshape(ref.shape), ref)
     h.close()
+
+
+@pytest.mark.parametrize("shape", [(128, 128, 128), (96, 96, 96)])    # both forms of the solver
+def test_poisson_source_in_pinned_memory(ry, shape):
+    """The source and the first guess are the caller's again after set_rhs."""
+    import torch
+    rng = np.random.default_rng(5)
+    b, x0 = rng.standard_normal(shape), rng.standard_normal(shape)
+    b -= b.mean()
+    out = []
+    for pinned in (False, True):
+        g = ry.Poisson(shape)
+        if pinned:
+            tb, tx = torch.from_numpy(b.copy()).pin_memory(), torch.from_numpy(x0.copy()).pin_memory()
+            assert ry.lib().ry_poisson_set_rhs(g.ctx, tb.data_ptr(), tx.data_ptr()) == ry.RY_OK
+            tx.numpy()[::-1] = np.nan
+            tb.numpy()[::-1] = np.nan
+        else:
+            g.set_rhs(b, x0)
+        g.iterate(3)
+        out.append([g.download("x"), g.download("r")])
+        g.close()
+    for x, y in zip(*out):
+        np.testing.assert_array_equal(x, y)
