@@ -417,8 +417,7 @@ ry_status enqueue_cfl_all(ry_ctx* c) {
 }
 
 // The launches of a one-level mesh, or a batch, that the caller has not tuned,
-// by its size
-// (FP64, us a step of chained steps: 1 / 2 / 4 wavefronts per 4^3-cell tile /
+// by its size (FP64, us a step of chained steps: 1 / 2 / 4 wavefronts per 4^3-cell tile /
 // 8^3-cell tile):
 //     512 tiles (32^3)    11.7 / 10.9 / 10.0 / 12.4
 //     729 tiles (36^3)    12.7 / 11.5 / 10.8 / 12.7
@@ -435,8 +434,11 @@ ry_status enqueue_cfl_all(ry_ctx* c) {
 // only while its launches are short (4^3- / 8^3-cell tiles: 42^3, 1.30 times
 // the cells: 13.5 / 11.7; 128 x 128 x 12, 1.33: 18.1 / 14.8), a fifth further
 // on (128 x 128 x 20, 5120 tiles, 1.20: 23.6 / 20.2; 92^3, 12,167, 1.14: 38.9 /
-// 35.9) and an eighth in the end (128^3 79.7 / 71.2; 64 boxes of 16 to 32
-// cells, 17,839, 1.21: 50.0 / 51.3).
+// 35.9) and an eighth in the end (128^3 79.7 / 71.2; 108^3, 1.115: 52.9 / 49.0;
+// 132 x 132 x 68, 1.124: 50.7 / 49.3), past which they are level (180 x 180 x
+// 36, 1.16: 48.2 / 48.3; 64 boxes of 16 to 32 cells, 17,839, 1.21: 50.0 / 51.3).
+// Not a choice of this rule: two wavefronts per 4^3-cell tile, 4 to 7% faster
+// than the 8^3-cell tile between 769 and about 1,050 tiles.
 constexpr ry_tuning kSmallTuning{1, 0, 4, 1, 4, 4}, kLargeTuning{1, 0, 4, 1, 8, 8};
 constexpr int32_t kSmallTilesPerCu = 3;
 

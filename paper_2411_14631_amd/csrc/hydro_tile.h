@@ -1243,7 +1243,10 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
       if (!f) continue;
       // a one-layer face state: the face between the cell and the core, whose
       // lower cell is this cell (lower layer) or the core cell below it
-      const LayerCell lc = layer_of(rnd);
+      // (where registers are short the entry is loaded again rather than kept)
+      constexpr bool AGAIN = K == 4 && NS > 0 && !ONE && NT == 64;
+      const int i = tid + NT * rnd;
+      const LayerCell lc = AGAIN ? layer_cell<K>(ST.b[AGAIN ? uint32_t(i - NCORE) : 0u], i) : layer_of(rnd);
       const int iw = lc.iw, dn = lc.dn;
       const bool up = lc.up;
       const int x = (iw % G::WB) - 1 - (up && dn == 0), y = (iw % G::WBB) / G::WB - 1 - (up && dn == 1),
@@ -1299,13 +1302,20 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
 // 256 threads (two cells per thread) the FP64 tile keeps 2 tiles per CU, 2
 // wavefronts per SIMD with up to 256 registers, the mixed tile 3 tiles per
 // CU (its LDS allows them) at 3 wavefronts per SIMD.
-template <typename Real, int K, int NS, int WPT>
+// With passive scalars the mixed form's registers decide: without a bound the
+// general kernels pass a step of the register file (one scalar 137, three 175)
+// and lose a wavefront per SIMD (eight steps of 112^3: one scalar 643 -> 583 us,
+// three 923 -> 790).
+template <typename Real, int K, int NS, int WPT, bool ONE>
 constexpr int hydro_waves_per_eu() {
-  return K == 8 ? (WPT == 8 ? 4 : (sizeof(Real) == 4 ? 3 : 2)) : (NS == 0 ? 3 : 1);
+  if (K == 8) return WPT == 8 ? 4 : (sizeof(Real) == 4 ? 3 : 2);
+  if (NS == 0) return 3;
+  if (sizeof(Real) == 8 || ONE) return 1;
+  return NS == 1 ? 4 : (NS < 4 ? 3 : 2);
 }
 
 template <typename Real, int TPW, int WPT, int NS, int K, bool ONE>
-__global__ __launch_bounds__(64 * WPT * TPW) __attribute__((amdgpu_waves_per_eu(hydro_waves_per_eu<Real, K, NS, WPT>())))
+__global__ __launch_bounds__(64 * WPT * TPW) __attribute__((amdgpu_waves_per_eu(hydro_waves_per_eu<Real, K, NS, WPT, ONE>())))
 void hydro_kernel(HydroArgs A) {
   constexpr int NT = 64 * WPT;
   __shared__ TileLDS<Real, NVAR + NS, K> S[TPW];
