@@ -1244,7 +1244,7 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
       // a one-layer face state: the face between the cell and the core, whose
       // lower cell is this cell (lower layer) or the core cell below it
       // (where registers are short the entry is loaded again rather than kept)
-      constexpr bool AGAIN = K == 4 && NS > 0 && !ONE && NT == 64;
+      constexpr bool AGAIN = K == 4 && !ONE && NT == 64 && (NS > 0 || sizeof(Real) == 4);
       const int i = tid + NT * rnd;
       const LayerCell lc = AGAIN ? layer_cell<K>(ST.b[AGAIN ? uint32_t(i - NCORE) : 0u], i) : layer_of(rnd);
       const int iw = lc.iw, dn = lc.dn;
