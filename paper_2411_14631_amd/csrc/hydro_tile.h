@@ -732,12 +732,15 @@ __device__ __forceinline__ int32_t lds_tab_entry(const HydroArgs& A, int32_t e) 
   return (e >= A.n_oct) ? e + A.ghost_adj : e;
 }
 
-// ONE: a step of a one-level run (Chain): lambda is formed here, every oct is
-// a leaf oct and the level has neither ghost octs nor registers.
-template <typename Real, int NT, int NS, int K, bool ONE>
+// The kinds of launch.  CHAINED (ONE): a step of a one-level run (Chain):
+// lambda is formed here, every oct is a leaf oct and the level has neither
+// ghost octs nor registers.  CHAINED_END: of one box, with a t_end.
+enum : int { GENERAL = 0, CHAINED = 1, CHAINED_END = 2 };
+template <typename Real, int NT, int NS, int K, int KIND>
 __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS<Real, NVAR + NS, K>& S, int tid_in,
                                            bool active, GatherRegs<K, NT, NVAR + NS>& R) {
   using G = Geom<K>;
+  constexpr bool ONE = KIND != GENERAL;
   constexpr int NV = NVAR + NS;
   constexpr int WSIZE = G::WSIZE, NFACE = G::NFACE, NUPPER = G::NUPPER, NCORE = G::NCORE;
   constexpr int NPOS_A = G::NPOS_A, NPOS_B = G::NPOS_B, TAB = G::TAB;
@@ -751,7 +754,7 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
   const int64_t P = A.plane;
   int nfl = 0;
   const uint32_t fl = active ? A.tflag[tile] : 0u;
-  const int past = ONE ? A.chain.rec_in[0].done : 0;
+  const int past = KIND == CHAINED_END ? A.chain.rec_in[0].done : 0;
   int hb[3];
   tile_hb<K>(fl, hb);
   const int box = (active && A.tile_box) ? A.tile_box[tile] : 0;
@@ -800,22 +803,6 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
     if (!debug_in_bounds(e_tab >= -1 && e_tab < A.n_ext, A.err)) e_tab = -1;
     S.tab[tid] = ONE ? e_tab : lds_tab_entry(A, e_tab);
   }
-  // chained steps enqueued past t_end (never a batch's): the record, the
-  // slots and the maxima are handed on and nothing else is read (us a step
-  // past the end, FP64, when the state was gathered first / now: 32^3 3.3 /
-  // 2.7, 128^3 30.6 / 5.7, 256^3 318 / 34).  Behind the table's store, so that
-  // a running step waits for the record and its table together
-  if constexpr (ONE) {
-    const Chain& C = A.chain;
-    if (C.t_end < INFINITY && past) {
-      if (tile == 0 && active && tid_in < 64) {
-        C.slots_clear[tid_in] = 0ull;
-        C.slots_out[tid_in] = C.slots_in[tid_in];
-        if (tid_in == 0) C.rec_out[0] = C.rec_in[0];
-      }
-      return;
-    }
-  }
   __syncthreads();
   // Wait for the table entries here on every path: otherwise the gather's
   // conditional state loads leave the compiler's load counting unsure of
@@ -825,6 +812,23 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
   for (int rnd = 0; rnd < NRA; ++rnd) asm volatile("" ::"v"(entA[rnd]));
 #pragma unroll
   for (int rnd = 0; rnd < NRB; ++rnd) asm volatile("" ::"v"(entB[rnd]));
+  // chained steps enqueued past t_end: the record, the slots and the maxima
+  // are handed on and nothing else is read (us a step past the end, FP64,
+  // when the state was gathered first / now: 32^3 3.3 / 2.7, 128^3 30.6 / 5.7,
+  // 256^3 318 / 34).  A kind of its own: the look at the record, loaded with
+  // the table and behind its barrier, costs a running step up to 1%
+  if constexpr (KIND == CHAINED_END) {
+    const Chain& C = A.chain;
+    if (__builtin_amdgcn_readfirstlane(past)) {
+      if (tile == 0 && active && tid_in < 64) {
+        C.slots_clear[tid_in] = 0ull;
+        C.slots_out[tid_in] = C.slots_in[tid_in];
+        if (tid_in == 0) C.rec_out[0] = C.rec_in[0];
+      }
+      return;
+    }
+  }
+
   // --- phase A: gather + primitives (all loads of the thread's positions
   // are issued before any conversion)
   gather_issue<K, NT, NV>(A, tab, fl, hb, tid, active, entA, R);
@@ -1306,27 +1310,27 @@ __device__ __forceinline__ void hydro_tile(const HydroArgs& A, int tile, TileLDS
 // general kernels pass a step of the register file (one scalar 137, three 175)
 // and lose a wavefront per SIMD (eight steps of 112^3: one scalar 643 -> 583 us,
 // three 923 -> 790).
-template <typename Real, int K, int NS, int WPT, bool ONE>
+template <typename Real, int K, int NS, int WPT, int KIND>
 constexpr int hydro_waves_per_eu() {
   if (K == 8) return WPT == 8 ? 4 : (sizeof(Real) == 4 ? 3 : 2);
   if (NS == 0) return 3;
-  if (sizeof(Real) == 8 || ONE) return 1;
+  if (sizeof(Real) == 8 || KIND != GENERAL) return 1;
   return NS == 1 ? 4 : (NS < 4 ? 3 : 2);
 }
 
-template <typename Real, int TPW, int WPT, int NS, int K, bool ONE>
-__global__ __launch_bounds__(64 * WPT * TPW) __attribute__((amdgpu_waves_per_eu(hydro_waves_per_eu<Real, K, NS, WPT, ONE>())))
+template <typename Real, int TPW, int WPT, int NS, int K, int KIND>
+__global__ __launch_bounds__(64 * WPT * TPW) __attribute__((amdgpu_waves_per_eu(hydro_waves_per_eu<Real, K, NS, WPT, KIND>())))
 void hydro_kernel(HydroArgs A) {
   constexpr int NT = 64 * WPT;
   __shared__ TileLDS<Real, NVAR + NS, K> S[TPW];
-  if (!ONE && A.skip && *A.skip) return;
+  if (KIND == GENERAL && A.skip && *A.skip) return;
   const int w = threadIdx.x / NT, tid = threadIdx.x % NT;
   const int ngroups = (A.n_tile + TPW - 1) / TPW;
   const int grp = xcd_remap(blockIdx.x, gridDim.x);
   if (grp >= ngroups) return;
   const int tile = grp * TPW + w;
   GatherRegs<K, NT, NVAR + NS> R;
-  hydro_tile<Real, NT, NS, K, ONE>(A, tile < A.n_tile ? tile : 0, S[w], tid, tile < A.n_tile, R);
+  hydro_tile<Real, NT, NS, K, KIND>(A, tile < A.n_tile ? tile : 0, S[w], tid, tile < A.n_tile, R);
 }
 
 // Persistent variant (K = 4): workgroups pop groups of tiles from 8 per-XCD
@@ -1377,7 +1381,7 @@ __global__ __launch_bounds__(64 * WPT * TPW) __attribute__((amdgpu_waves_per_eu(
       if (grp >= ngroups) break;
       const int tile = grp * TPW + w;
       GatherRegs<4, NT, NVAR> R;
-      hydro_tile<Real, NT, 0, 4, false>(A, tile < A.n_tile ? tile : 0, S[w], tid, tile < A.n_tile, R);
+      hydro_tile<Real, NT, 0, 4, GENERAL>(A, tile < A.n_tile ? tile : 0, S[w], tid, tile < A.n_tile, R);
     }
     if (threadIdx.x == 0) {
       int next = -1;
@@ -1405,10 +1409,10 @@ static int launch_hydro_t(const HydroArgs& a, const ry_tuning& t, int num_cu, hi
   const int ngroups = (a.n_tile + TPW - 1) / TPW;
   if (ngroups == 0) return 0;
   if (NS > 0 || K != 4 || !t.persistent) {
-    if (a.chain.slots_in)
-      hipLaunchKernelGGL((hydro_kernel<Real, TPW, WPT, NS, K, true>), dim3(ngroups), dim3(64 * WPT * TPW), 0, s, a);
-    else
-      hipLaunchKernelGGL((hydro_kernel<Real, TPW, WPT, NS, K, false>), dim3(ngroups), dim3(64 * WPT * TPW), 0, s, a);
+    const dim3 g(ngroups), b(64 * WPT * TPW);
+    if (!a.chain.slots_in) hipLaunchKernelGGL((hydro_kernel<Real, TPW, WPT, NS, K, GENERAL>), g, b, 0, s, a);
+    else if (a.chain.t_end < INFINITY) hipLaunchKernelGGL((hydro_kernel<Real, TPW, WPT, NS, K, CHAINED_END>), g, b, 0, s, a);
+    else hipLaunchKernelGGL((hydro_kernel<Real, TPW, WPT, NS, K, CHAINED>), g, b, 0, s, a);
   } else if constexpr (NS == 0 && K == 4) {
     const int batch = t.batch > 0 ? t.batch : 1;
     const int nitems = (ngroups + batch - 1) / batch;
