@@ -2152,14 +2152,16 @@ ry_status ry_autotune(ry_ctx* c, ry_tuning* best, double* times_ms, int32_t max_
   if (!c || !c->built) return RY_EINVAL;
   if (c->nlev == 1) {
     // the timed steps are whole ones: every kind finds the state's maxima
-    // where it reads them, and a clock without an end
-    ry_status s0 = enqueue_cfl_all(c);
+    // where it reads them, and a clock without an end.  The chained ones read
+    // phase 0's slots, which none of them writes: they stay the state's
+    ry_status s0 = c->slots_valid ? RY_OK : enqueue_cfl_all(c);
     if (!s0) s0 = chain_begin(c, 0.0);
     if (s0) return s0;
     if (!c->batch &&
         launch_begin(0.0, INFINITY, probe_clock(c), reinterpret_cast<int32_t*>(c->d_partial), c->stream))
       return fail(c, RY_EHIP, "begin kernel");
-    c->slots_valid = c->smax_valid = c->chain_valid = false;
+    c->slots_valid = c->smax_valid = false;
+    c->chain_valid = true;
   }
   std::vector<ry_tuning> cand;
   for (int wpt : {1, 2, 4})
