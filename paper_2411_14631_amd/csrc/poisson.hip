@@ -21,7 +21,7 @@
 //              halo, x_{i+1}, partials of gamma_{i+1} = r_{i+1}.(M^-1 r_{i+1}).
 // 64 bytes per cell (r, p read and p written; p, r, x read and r, x written).
 // r and p are double-buffered: neighbouring workgroups read the old one.
-// Measured per iteration: 256^3 238 us (pipelined, with its scalar step in a
+// Measured per iteration: 256^3 243 us (pipelined, with its scalar step in a
 // launch of its own: 420; a 1 GiB device copy runs at 5.07 TB/s, at which 64
 // bytes per cell take 212 us), 160^3 60 us (117), 128^3 40 us (60).
 //
@@ -527,8 +527,8 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(MANY ? 6 : 
 }
 
 // ---------------------------------------------------------------------------
-// The two sweeps of the large problems.  Bound: HBM (256^3: direction 96 us
-// for 403 MB, update 134 us for 671 MB: 4.2 and 5.0 TB/s).  The direction
+// The two sweeps of the large problems.  Bound: HBM (256^3: direction 105 us
+// for 403 MB, update 137 us for 671 MB: 3.8 and 4.9 TB/s).  The direction
 // sweep marches down, so that it starts on the planes the update sweep left
 // in the caches (1.5% at 256^3).
 // ---------------------------------------------------------------------------
