@@ -1127,9 +1127,14 @@ ry_status finish_regrid(ry_ctx* c, bool device, const std::vector<uint8_t*>* dir
   for (int k = 0; k < nl; ++k) c->seg_off.push_back(c->seg_off.back() + part_slots(c->lev[k]));
   if (c->seg_off.back() > c->part_cap) {
     dfree(c, c->d_part);
-    // an eighth more than asked for: the mesh changes by a few percent
+    // an eighth more than asked for, where there is room: the mesh changes by
+    // a few percent
     c->part_cap = c->seg_off.back() + c->seg_off.back() / 8;
     c->d_part = static_cast<double*>(dalloc(c, sizeof(double) * c->part_cap));
+    if (!c->d_part) {
+      c->part_cap = c->seg_off.back();
+      c->d_part = static_cast<double*>(dalloc(c, sizeof(double) * c->part_cap));
+    }
     if (!c->d_part) {
       free_all(c);
       c->built = false;

@@ -31,7 +31,7 @@ class Memory:
         hip = ry.lib()
         hip.hipMalloc.argtypes = [C.POINTER(C.c_void_p), C.c_size_t]
         hip.hipFree.argtypes = [C.c_void_p]
-        self.refuse, self.refused = set(refuse), []
+        self.refuse, self.refused, self.log, size = set(refuse), [], [], {}
 
         def alloc(n, user):
             p = C.c_void_p()
@@ -39,9 +39,14 @@ class Memory:
             if bad:
                 self.refused.append(n)
             rc = hip.hipMalloc(C.byref(p), C.c_size_t(1 << 60 if bad else n))
-            return p.value if rc == 0 else None
+            self.log.append(("alloc", n))
+            if rc:
+                return None
+            size[p.value] = n
+            return p.value
 
         def free(p, user):
+            self.log.append(("free", size.pop(p)))
             hip.hipFree(p)
 
         self.alloc_cb = ry.ALLOC_FN(alloc)
@@ -103,3 +108,39 @@ def test_poisson_after_a_refused_one(ry, monkeypatch):
     g.set_rhs(b)
     assert g.solve(1e-6, 200) > 0
     g.close()
+
+
+def test_regrid_takes_what_it_needs(ry):
+    """A growing mesh asks for an eighth more CFL partials than it needs;
+    refused, for what it needs."""
+    import cases
+    prob = cases.amr_blob(level_min=4, level_max=6)
+    runs, part = [], None
+    for refuse in (False, True):
+        mem = Memory(ry)
+        h = ry.Hydro(prob, memory=mem)
+        # the partials follow the levels' maxima and their slots
+        sizes = [n for what, n in mem.log if what == "alloc"]
+        i = next(i for i in range(len(sizes) - 1) if sizes[i] == 8 * 3 and sizes[i + 1] % (8 * 3 * 64) == 0)
+        old = sizes[i + 2]
+        h.set_refine_param(0.25 * prob.refine_param)
+        del mem.log[:]
+        if refuse:
+            mem.refuse.add(part)
+        h.regrid()
+        if not refuse:
+            part = next(b[1] for a, b in zip(mem.log, mem.log[1:]) if a == ("free", old) and b[0] == "alloc")
+            assert part > old
+        else:
+            assert mem.refused == [part]
+            k = mem.log.index(("alloc", part))
+            need = mem.log[k + 1][1] // 8
+            assert need + need // 8 == part // 8
+            mem.refuse.clear()
+        h.advance(3)
+        h.regrid()
+        h.advance(2)
+        runs.append([h.download(lv) for lv in h.levels])
+        h.close()
+    for a, b in zip(*runs):
+        np.testing.assert_array_equal(a, b)
